@@ -10,10 +10,12 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdwfmm.so")
 OBJDIR = os.path.join(HERE, "..", "_build")
-# (source, object, extra flags): kernels.hip is compiled in two parts (single-problem and
-# batched entry points) so the two halves of its template instantiations build in parallel
+# (source, object, extra flags): kernels.hip is compiled in parts so that its template
+# instantiations build in parallel
 UNITS = [("kernels.hip", "kernels_single.o", ["-DDWFMM_KERNELS_PART=1"]),
          ("kernels.hip", "kernels_batch.o", ["-DDWFMM_KERNELS_PART=2"]),
+         ("kernels.hip", "kernels_eval.o", ["-DDWFMM_KERNELS_PART=3"]),
+         ("kernels.hip", "kernels_lp.o", ["-DDWFMM_KERNELS_PART=4"]),
          ("api.hip", "api.o", []),
          ("setup.cpp", "setup.o", [])]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -184,6 +184,18 @@ extern "C" dwfmm_status dwfmm_build_tree_ex(const double *points, int64_t n, int
     return tree_from_host(pts, n, d, dim_weights, leaf_size, eta, st, out, (int)admissibility);
 }
 
+// Pieces of at most 128 points (the rows of one nearfield workgroup) a leaf is taken in.
+static int leaf_pieces(int max_leaf) { return std::max(1, (max_leaf + 127) / 128); }
+
+// Per-piece work from per-leaf work: entry ppl * leaf + piece.
+static std::vector<double> piece_work(const std::vector<double> &w, int ppl)
+{
+    std::vector<double> p;
+    p.reserve(w.size() * ppl);
+    for (double v : w) p.insert(p.end(), ppl, v / ppl);
+    return p;
+}
+
 // Launch order of the leaves of a nearfield kernel with per-leaf work w: workgroup q runs on XCD
 // q mod 8, so the leaves are cut into 8 contiguous segments of equal work, segment k dealt to XCD
 // k (each XCD's L2 then holds the sources of one region of the tree), the costliest leaves first
@@ -309,8 +321,9 @@ static dwfmm_status tree_host(const std::vector<double> &pts, int64_t n, int32_t
         }
         t->leaf_work = lw;
         S.leaf_order = xcd_order(lw);
-        S.near_order = xcd_order(nw);
-        S.near_order_seq = xcd_order(nw, false);
+        const std::vector<double> pw = piece_work(nw, leaf_pieces(S.max_leaf));
+        S.near_order = xcd_order(pw);
+        S.near_order_seq = xcd_order(pw, false);
     }
     std::vector<double> &center = S.center, rad(H.nleaf, 0.0);
     center.assign((size_t)H.nleaf * dp, 0.0);
@@ -387,6 +400,7 @@ static dwfmm_status tree_upload(dwfmm_tree t, hipStream_t st)
     D.ncl = (int)H.ncl;
     D.leaf_first = (int)(H.nleaf - 1);
     D.max_leaf = S.max_leaf;
+    D.ppl = leaf_pieces(S.max_leaf);
     D.min_far_level = H.min_far_level;
     D.Xs = dXs;
     D.perm = dperm;
@@ -2510,7 +2524,7 @@ extern "C" dwfmm_status dwfmm_eval_create(dwfmm_op op, const double *targets, in
             for (int32_t q = nptr_leaf[l]; q < nptr_leaf[l + 1]; ++q) ns += Hs.end[H.Nsrc[q]] - Hs.begin[H.Nsrc[q]];
             nw[l] = (double)(H.end[lf + l] - H.begin[lf + l]) * (ns + 128.0);
         }
-        near_order = xcd_order(nw);
+        near_order = xcd_order(piece_work(nw, leaf_pieces(max_leaf)));
     }
     std::vector<double> nodes, nodes_p((size_t)H.ncl * nx * dp, 0.0), E;
     box_nodes(H, op->B, nodes);
@@ -2563,6 +2577,7 @@ extern "C" dwfmm_status dwfmm_eval_create(dwfmm_op op, const double *targets, in
     D.ncl = (int)H.ncl;
     D.leaf_first = lf;
     D.max_leaf = max_leaf;
+    D.ppl = leaf_pieces(max_leaf);
     D.min_far_level = H.min_far_level;
     D.Xs = dXs;
     D.perm = dperm;

@@ -36,6 +36,9 @@ struct DevTree {
     // The same for the several-rhs nearfield, which sweeps each target leaf's whole nearfield list:
     // segments of equal list entries, costliest leaf first; near_order_seq has the same segments in
     // leaf order (the launches that read stored BF16 tiles, whose sources then stay in L2).
+    // Leaves of more than 128 points are taken as ppl = ceil(max_leaf / 128) pieces each: an entry is
+    // ppl * leaf + piece (ppl = 1 otherwise).
+    int ppl;
     const int32_t *near_order;
     const int32_t *near_order_seq;
     int n_near_order;
@@ -104,6 +107,20 @@ hipError_t launch_matvec(const DevTree &T, const DevOp &O, const double *x, doub
 // Ts/Os: the source tree and operator, whose charge and moment workspace it uses.
 hipError_t launch_eval(const DevTree &Tt, const DevOp &Ot, const DevTree &Ts, const DevOp &Os, const double *x,
                        double *y, int nrhs, hipStream_t stream);
+
+// Parts of the two above that are compiled apart (kernels.hip).  launch_pieces: FP64 nearfield of
+// targets T/O over sources Ts/xs (charges in source tree order) in pieces of at most 128 targets,
+// any nrhs, with L2P if far; launch_m2l_wide: FP64 coupling of up to 128 nodes, any nrhs;
+// launch_m2l_mrhs, launch_mrhs_lp: the several-rhs coupling (n_x <= 32) and the FP32/BF16
+// several-rhs nearfield of the matvec.  Radial kernels, d <= 32.
+hipError_t launch_pieces(const DevTree &T, const DevOp &O, const DevTree &Ts, const double *xs, double *y, int nrhs,
+                         int near, int far, hipStream_t stream);
+hipError_t launch_m2l_wide(const DevTree &T, const DevOp &Ot, const DevOp &Os, int first, int cnt, int nrhs,
+                           hipStream_t stream);
+hipError_t launch_m2l_mrhs(const DevTree &T, const DevOp &O, int first, int cnt, int nrhs, int precision,
+                           hipStream_t stream);
+hipError_t launch_mrhs_lp(const DevTree &T, const DevOp &O, double *y, int nrhs, int near, int far, int precision,
+                          hipStream_t stream);
 
 // Lagrange basis cache Lb from the boxes and the index set (setup).
 hipError_t launch_basis(const DevTree &T, int nx, const double *clo, const double *csc, const double *coff,

@@ -248,7 +248,7 @@ __global__ __launch_bounds__(256) void p2m_kernel(DevTree T, DevOp O, const doub
 
 // P2M for several rhs: the leaf's whole block of charges is staged once (rows of nrhs
 // doubles, read and written in order), then every (node, rhs) moment sums over the leaf's
-// points from LDS, in point order.  For leaves of at most 4096 / nrhs points.
+// points from LDS, in point order.  For leaves of at most 8192 / nrhs points (64 KB of LDS).
 __global__ __launch_bounds__(256) void p2m_multi_kernel(DevTree T, DevOp O, const double *__restrict__ x, int nrhs,
                                                         int do_far)
 {
@@ -272,6 +272,15 @@ __global__ __launch_bounds__(256) void p2m_multi_kernel(DevTree T, DevOp O, cons
         for (int i = 0; i < np; ++i) s = fma(lb[i], xl[i * nrhs + r], s);
         O.M[((size_t)c * nx + a) * nrhs + r] = s;
     }
+}
+
+void launch_p2m(const DevTree &T, const DevOp &O, const double *x, int nrhs, int do_far, hipStream_t st)
+{
+    if (nrhs > 1 && T.max_leaf * nrhs <= 8192)
+        hipLaunchKernelGGL(p2m_multi_kernel, dim3(T.nleaf), dim3(256), sizeof(double) * T.max_leaf * nrhs, st, T, O, x,
+                           nrhs, do_far);
+    else
+        hipLaunchKernelGGL(p2m_kernel, dim3(T.nleaf), dim3(256), sizeof(double) * T.max_leaf, st, T, O, x, nrhs, do_far);
 }
 
 // ---------------------------------------------------------------- M2M, one level
@@ -1242,16 +1251,37 @@ hipError_t launch_cross_mfma_k(const DevTree &Tt, const DevOp &Ot, const DevTree
 // halves (r ^ 16), so that the two lane groups of a half-wave (rows j and j + 1 of a tile
 // column) read opposite halves of the 64 banks.  Coordinates [k][j] in rows of kSX64 doubles,
 // 16 past the leaf size for the same reason.
+// RB = 0 is one rhs: there is no product for an MFMA, the charges are one column and each lane
+// sums its target's entries on the vector ALU (racc).
 template <int RB>
-constexpr int q_stride() { return 16 * RB; }
+constexpr int q_stride() { return RB == 0 ? 1 : 16 * RB; }
 template <int RB>
 __device__ __forceinline__ int q_col(int j, int r) { return RB == 2 ? r ^ ((j & 1) << 4) : r; }
 constexpr int kSX64 = kSymLeaf + 16;
 
-template <int KIND, int DK, int RB, bool DIAG>
-__device__ __forceinline__ void mrhs_block(const double (&Bt)[2][DK / 4], const double (&tn)[2], dbl4 (&Y)[2][RB],
-                                           const double *sX, const double *sN, const double *sQ, int ns, int ntiles,
-                                           int w, int li, int lg, double inv_ell)
+// The squared distance of target i (of tree T, shifted by cen) and staged source column j from the
+// coordinate differences themselves.  With the Gram form the rounding of |x|^2 + |y|^2 - 2 x.y is
+// that of the norms, which the exponential kernel's sqrt turns into an error of the kernel value
+// for nearly coincident points; the caller takes this form there (1e-4 of the norms and below: rare
+// in more than two dimensions, and the error it leaves elsewhere is 5e-14 of the points' distance
+// from the shift over ell).
+template <int DK>
+__device__ __forceinline__ double r2_direct(const DevTree &T, const double *cen, int i, const double *sX, int j)
+{
+    double r2 = 0.0;
+    for (int k = 0; k < DK; ++k) {
+        const double t = (T.Xs[(size_t)k * T.n + i] - cen[k]) - sX[k * kSX64 + j];
+        r2 = fma(t, t, r2);
+    }
+    return r2;
+}
+
+// near_i (cross form, exponential kernel): the tree positions of this lane's two targets.
+template <int KIND, int DK, int RB, bool DIAG, bool CROSS>
+__device__ __forceinline__ void mrhs_block(const double (&Bt)[2][DK / 4], const double (&tn)[2], dbl4 (&Y)[2][RB == 0 ? 1 : RB],
+                                           double (&racc)[2], const double *sX, const double *sN, const double *sQ,
+                                           int ns, int ntiles, int w, int li, int lg, double inv_ell,
+                                           const DevTree &T, const double *cen, const int (&near_i)[2])
 {
     constexpr int NKC = DK / 4;
     const int rt[2] = {w, w + 4};
@@ -1263,12 +1293,16 @@ __device__ __forceinline__ void mrhs_block(const double (&Bt)[2][DK / 4], const 
         double snv[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) snv[v] = sN[16 * ct + 4 * v + lg];
-        double Qf[RB][4];
+        double Qf[RB == 0 ? 1 : RB][4];
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
             for (int v = 0; v < 4; ++v)
                 Qf[rb][v] = sQ[(16 * ct + 4 * v + lg) * q_stride<RB>() + q_col<RB>(lg, 16 * rb + li)];
+        if constexpr (RB == 0) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) Qf[0][v] = sQ[16 * ct + 4 * v + lg];
+        }
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             if (rt[u] >= ntiles) continue;  // uniform over the wave
@@ -1292,8 +1326,15 @@ __device__ __forceinline__ void mrhs_block(const double (&Bt)[2][DK / 4], const 
                     if constexpr (DIAG) {
                         if (16 * rt[u] + li == 16 * ct + 4 * v + lg) r2 = 0.0;
                     }
+                    if constexpr (CROSS && KIND == 2) {
+                        if (r2 <= 1e-4 * (tn[u] + snv[v])) r2 = r2_direct<DK>(T, cen, near_i[u], sX, 16 * ct + 4 * v + lg);
+                    }
                     Kv[v] = kernel_fast<KIND>(r2, inv_ell);
                 }
+            }
+            if constexpr (RB == 0) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) racc[u] = fma(Kv[v], Qf[0][v], racc[u]);
             }
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb)
@@ -1303,39 +1344,57 @@ __device__ __forceinline__ void mrhs_block(const double (&Bt)[2][DK / 4], const 
     }
 }
 
-template <int KIND, int DK, int RB>
-__global__ __launch_bounds__(256) void p2p_mrhs_kernel(DevTree T, DevOp O, double *__restrict__ y, int nrhs,
-                                                       int do_near, int do_far)
+// CROSS: targets T/O and sources Ts/xs (charges in source tree order) may be different trees, a
+// target leaf of more than kSymLeaf points is taken as T.ppl pieces (one workgroup each, whole row
+// tiles, sizes even), and the leaf's own block is part of the stream.
+template <int KIND, int DK, int RB, bool CROSS>
+__device__ __forceinline__ void p2p_mrhs_body(const DevTree &T, const DevOp &O, const DevTree &Ts,
+                                              const double *__restrict__ xs, double *__restrict__ y, int nrhs,
+                                              int do_near, int do_far)
 {
     constexpr int NKC = DK / 4;
     __shared__ double sX[DK * kSX64];
     __shared__ double sN[kSymLeaf];
-    __shared__ double sQ[kSymLeaf * q_stride<RB>()];
+    __shared__ double sQ[kSymLeaf * q_stride<RB>()];  // charges [j][r]
     __shared__ double cen[DK];
     __shared__ int32_t sPre[kSymSeg + 1], sBeg[kSymSeg], colP[kSymLeaf], sDiag;
     constexpr bool kSplit = KIND == kGaussSplit;
     __shared__ double tF[kSplit ? kSymLeaf : 1];  // split Gaussian: row factors exp(-|x - c|^2 / ell)
-    const int l = T.near_order[blockIdx.x];
+    int l = T.near_order[blockIdx.x];
     if (l < 0) return;  // padding of a shorter XCD segment
+    int cb, nt;  // this workgroup's targets: tree positions [cb, cb + nt)
+    if constexpr (CROSS) {
+        const int part = l % T.ppl;
+        l /= T.ppl;
+        const int beg = T.cbeg[T.leaf_first + l], all = T.cend[T.leaf_first + l] - beg;
+        const int per = ((all + T.ppl - 1) / T.ppl + 15) / 16 * 16;  // at most kSymLeaf
+        cb = beg + part * per;
+        nt = min(per, all - part * per);
+    } else {
+        cb = T.cbeg[T.leaf_first + l];
+        nt = T.cend[T.leaf_first + l] - cb;
+    }
     const int c = T.leaf_first + l;
-    const int cb = T.cbeg[c], nt = T.cend[c] - cb;
-    if (nt == 0) return;
+    if (nt <= 0) return;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int li = lane & 15, lg = lane >> 4;
-    const int n = T.n;
+    const int n = T.n, ns_all = CROSS ? Ts.n : n;
     const double inv_ell = 1.0 / O.ell;
     const int ntiles = (nt + 15) / 16;
-    if (tid < DK) cen[tid] = T.center[(size_t)l * DK + tid];
+    // the shift: the leaf's box midpoint, or (target trees of evaluation plans) the first target
+    if (tid < DK) cen[tid] = !CROSS || T.center ? T.center[(size_t)l * DK + tid] : T.Xs[(size_t)tid * n + cb];
     __syncthreads();
     // targets as the B operand: lane (i + 16 g) holds coordinate 4 kc + g of target i
     const int rt[2] = {w, w + 4};
-    double Bt[2][NKC], tn[2];
-    dbl4 Y[2][RB];
+    double Bt[2][NKC], tn[2], racc[2] = {0.0, 0.0};
+    dbl4 Y[2][RB == 0 ? 1 : RB];
+    int near_i[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         const int i = 16 * rt[u] + li;
         const bool ok = i < nt;
         const int ii = cb + (ok ? i : nt - 1);
+        near_i[u] = ii;
         double s = 0.0;
 #pragma unroll
         for (int k = 0; k < DK; ++k) {
@@ -1368,11 +1427,13 @@ __global__ __launch_bounds__(256) void p2p_mrhs_kernel(DevTree T, DevOp O, doubl
         // the leaf's own block first (when listed), then the other source leaves as one stream of
         // points, kSymLeaf columns at a time (only the stream's last column tile is padded)
         const int f0 = T.Nptr[l], f1 = T.Nptr[l + 1];
-        if (tid == 0) sDiag = 0;
-        __syncthreads();
-        for (int f = f0 + tid; f < f1; f += blockDim.x)
-            if (T.Nsrc[f] == l) sDiag = 1;
-        __syncthreads();
+        if constexpr (!CROSS) {
+            if (tid == 0) sDiag = 0;
+            __syncthreads();
+            for (int f = f0 + tid; f < f1; f += blockDim.x)
+                if (T.Nsrc[f] == l) sDiag = 1;
+            __syncthreads();
+        }
         // columns [c0, c0 + ns) of the current stream (or of the own block): colP holds each
         // column's point, set by the caller of stage_chunk before the barrier
         // sid: the 128 threads that stage the coordinates (waves 0-1 or 2-3, alternating by chunk)
@@ -1383,7 +1444,8 @@ __global__ __launch_bounds__(256) void p2p_mrhs_kernel(DevTree T, DevOp O, doubl
                 const int jj = colP[j];
                 double xv[DK];
 #pragma unroll
-                for (int k = 0; k < DK; ++k) xv[k] = T.Xs[(size_t)k * n + jj];
+                for (int k = 0; k < DK; ++k) xv[k] = (CROSS ? Ts.Xs : T.Xs)[(size_t)k * ns_all + jj];
+                const double q1 = RB == 0 ? xs[jj] : 0.0;
                 double s = 0.0;
 #pragma unroll
                 for (int k = 0; k < DK; ++k) {
@@ -1393,27 +1455,32 @@ __global__ __launch_bounds__(256) void p2p_mrhs_kernel(DevTree T, DevOp O, doubl
                 }
                 // split Gaussian: the base-2 logarithm of the column factor exp(-|y - c|^2 / ell)
                 sN[j] = kSplit ? s * (-1.4426950408889634 * inv_ell) : s;
+                if constexpr (RB == 0) sQ[j] = ok ? q1 : 0.0;
             }
             // charges [j][r], zero beyond the stream and beyond nrhs: thread tid stages rhs
             // r = tid % 16RB of columns j0 + t * 256 / 16RB, every load issued before the first store
-            constexpr int QPT = kSymLeaf * 16 * RB / 256;
-            const int r = tid % (16 * RB), j0 = tid / (16 * RB);
-            const int rr = r < nrhs ? r : 0;
-            double qv[QPT];
+            if constexpr (RB > 0) {
+                constexpr int W = 16 * RB, QPT = kSymLeaf * W / 256;
+                const int r = tid % W, j0 = tid / W;
+                const int rr = r < nrhs ? r : 0;
+                double qv[QPT];
 #pragma unroll
-            for (int t = 0; t < QPT; ++t) qv[t] = O.xt[(size_t)colP[j0 + t * (256 / (16 * RB))] * nrhs + rr];
+                for (int t = 0; t < QPT; ++t) qv[t] = xs[(size_t)colP[j0 + t * (256 / W)] * nrhs + rr];
 #pragma unroll
-            for (int t = 0; t < QPT; ++t) {
-                const int j = j0 + t * (256 / (16 * RB));
-                sQ[j * q_stride<RB>() + q_col<RB>(j, r)] = (j < ns && r < nrhs) ? qv[t] : 0.0;
+                for (int t = 0; t < QPT; ++t) {
+                    const int j = j0 + t * (256 / W);
+                    sQ[j * q_stride<RB>() + q_col<RB>(j, r)] = (j < ns && r < nrhs) ? qv[t] : 0.0;
+                }
             }
         };
-        if (sDiag) {
-            if (tid < kSymLeaf) colP[tid] = cb + (tid < nt ? tid : nt - 1);
-            __syncthreads();
-            stage_chunk(nt, tid);
-            __syncthreads();
-            mrhs_block<KIND, DK, RB, true>(Bt, tn, Y, sX, sN, sQ, nt, ntiles, w, li, lg, inv_ell);
+        if constexpr (!CROSS) {
+            if (sDiag) {
+                if (tid < kSymLeaf) colP[tid] = cb + (tid < nt ? tid : nt - 1);
+                __syncthreads();
+                stage_chunk(nt, tid);
+                __syncthreads();
+                mrhs_block<KIND, DK, RB, true, false>(Bt, tn, Y, racc, sX, sN, sQ, nt, ntiles, w, li, lg, inv_ell, T, cen, near_i);
+            }
         }
         int chunk = 0;  // the column search and coordinate staging alternate between waves 0-1 and 2-3
         for (int fb = f0; fb < f1; fb += kSymSeg) {
@@ -1424,8 +1491,9 @@ __global__ __launch_bounds__(256) void p2p_mrhs_kernel(DevTree T, DevOp O, doubl
                 const int f = fb + tid;
                 if (f < fe) {
                     const int sl = T.Nsrc[f];
-                    beg = T.cbeg[T.leaf_first + sl];
-                    if (sl != l) sz = T.cend[T.leaf_first + sl] - beg;
+                    const DevTree &S = CROSS ? Ts : T;
+                    beg = S.cbeg[S.leaf_first + sl];
+                    if (CROSS || sl != l) sz = S.cend[S.leaf_first + sl] - beg;
                 }
                 sPre[tid + 1] = sz;
                 sBeg[tid] = beg;
@@ -1446,7 +1514,7 @@ __global__ __launch_bounds__(256) void p2p_mrhs_kernel(DevTree T, DevOp O, doubl
                 // read (its staging, which does, ended at the barrier before them), and the barrier after
                 // the search keeps this chunk's staging behind every wave's previous tiles
                 if (sid < kSymLeaf) {
-                    int pidx = cb;  // any valid point for the padding columns
+                    int pidx = CROSS ? 0 : cb;  // any valid point for the padding columns
                     if (sid < ns) {
                         const int col = c0 + sid;  // the entry holding it: the largest k with sPre[k] <= col
                         int lo = 0, hi = kSymSeg;
@@ -1462,11 +1530,33 @@ __global__ __launch_bounds__(256) void p2p_mrhs_kernel(DevTree T, DevOp O, doubl
                 __syncthreads();
                 stage_chunk(ns, sid);
                 __syncthreads();
-                mrhs_block<KIND, DK, RB, false>(Bt, tn, Y, sX, sN, sQ, ns, ntiles, w, li, lg, inv_ell);
+                mrhs_block<KIND, DK, RB, false, CROSS>(Bt, tn, Y, racc, sX, sN, sQ, ns, ntiles, w, li, lg, inv_ell, T, cen,
+                                                       near_i);
             }
         }
     }
     if constexpr (kSplit) __syncthreads();  // tF is complete
+    if constexpr (RB == 0) {
+        // lane (i + 16 g) holds the entries of sources 4 v + g of target i
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (rt[u] >= ntiles) continue;  // uniform over the wave
+            double acc = racc[u];
+            acc += __shfl_xor(acc, 16, 64);
+            acc += __shfl_xor(acc, 32, 64);
+            const int i = 16 * rt[u] + li;
+            if (lg != 0 || i >= nt) continue;
+            if constexpr (kSplit) acc *= tF[i];
+            if (do_far) {
+                const double *lc = O.L + (size_t)c * O.nx;
+                double fs = 0.0;
+                for (int a = 0; a < O.nx; ++a) fs = fma(O.Lb[(size_t)a * n + cb + i], lc[a], fs);
+                acc += fs;
+            }
+            y[T.perm[cb + i]] = acc;
+        }
+        return;
+    }
     // Y[u][rb] element v of lane (r + 16 g) is output (target 16 rt + 4 v + g, rhs 16 rb + r)
     const double *lc = O.L + (size_t)c * O.nx * nrhs;
 #pragma unroll
@@ -1491,6 +1581,53 @@ __global__ __launch_bounds__(256) void p2p_mrhs_kernel(DevTree T, DevOp O, doubl
             }
         }
     }
+}
+
+template <int KIND, int DK, int RB>
+__global__ __launch_bounds__(256) void p2p_mrhs_kernel(DevTree T, DevOp O, double *__restrict__ y, int nrhs,
+                                                       int do_near, int do_far)
+{
+    p2p_mrhs_body<KIND, DK, RB, false>(T, O, T, O.xt, y, nrhs, do_near, do_far);
+}
+
+// Nearfield of evaluation plans with several rhs or large target leaves, and of trees whose leaves
+// exceed kSymLeaf points (then Ts = T): bound by the FP64 pipe as the kernel above.  These calls ran
+// one target per lane on the general kernel, entries recomputed for every rhs: N = 1e5, d = 20,
+// exponential, leaf 256, 25 rhs 223.6 -> 4.6 ms; 1e5 sources, 5e4 targets, d = 10 Matern, 8 rhs
+// 69.6 -> 2.0 ms.
+template <int KIND, int DK, int RB>
+__global__ __launch_bounds__(256) void p2p_pieces_kernel(DevTree T, DevOp O, DevTree Ts, const double *__restrict__ xs,
+                                                         double *__restrict__ y, int nrhs, int do_near, int do_far)
+{
+    p2p_mrhs_body<KIND, DK, RB, true>(T, O, Ts, xs, y, nrhs, do_near, do_far);
+}
+
+template <int KIND, int DK>
+void launch_pieces_d(const DevTree &T, const DevOp &O, const DevTree &Ts, const double *xs, double *y, int nrhs,
+                     int near, int far, hipStream_t st)
+{
+    const dim3 g(T.n_near_order), b(256);
+    if (nrhs == 1)
+        hipLaunchKernelGGL((p2p_pieces_kernel<KIND, DK, 0>), g, b, 0, st, T, O, Ts, xs, y, nrhs, near, far);
+    else if (nrhs <= 16)
+        hipLaunchKernelGGL((p2p_pieces_kernel<KIND, DK, 1>), g, b, 0, st, T, O, Ts, xs, y, nrhs, near, far);
+    else if constexpr (DK <= 28)
+        hipLaunchKernelGGL((p2p_pieces_kernel<KIND, DK, 2>), g, b, 0, st, T, O, Ts, xs, y, nrhs, near, far);
+}
+
+template <int KIND>
+hipError_t launch_pieces_k(const DevTree &T, const DevOp &O, const DevTree &Ts, const double *xs, double *y, int nrhs,
+                           int near, int far, hipStream_t st)
+{
+    switch (T.dpad) {
+#define DWFMM_PC(D) \
+    case D: launch_pieces_d<KIND, D>(T, O, Ts, xs, y, nrhs, near, far, st); break;
+        DWFMM_PC(4) DWFMM_PC(8) DWFMM_PC(12) DWFMM_PC(16) DWFMM_PC(20) DWFMM_PC(24) DWFMM_PC(28) DWFMM_PC(32)
+#undef DWFMM_PC
+    default:
+        return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
 }
 
 template <int KIND, int DK>
@@ -2397,8 +2534,9 @@ struct m2l_types<0> {
     typedef dbl4 V;
 };
 
+// O/Os: target and source side (the same operator for the matvec; T's lists name source clusters).
 template <int KIND, int DK, int PREC>
-__global__ __launch_bounds__(256) void m2l_mrhs_kernel(DevTree T, DevOp O, int first, int nrhs)
+__device__ __forceinline__ void m2l_mrhs_body(const DevTree &T, const DevOp &O, const DevOp &Os, int first, int nrhs)
 {
     typedef typename m2l_types<PREC>::T R;
     typedef typename m2l_types<PREC>::V V4;
@@ -2427,8 +2565,8 @@ __global__ __launch_bounds__(256) void m2l_mrhs_kernel(DevTree T, DevOp O, int f
     }
     for (int f = f0 + w; f < f1; f += 4) {
         const int s = T.Fsrc[f];
-        const double *snode = O.nodesT + (size_t)s * DK * nxp;
-        const double *ms = O.M + (size_t)s * nx * nrhs;
+        const double *snode = Os.nodesT + (size_t)s * DK * nxp;
+        const double *ms = Os.M + (size_t)s * nx * nrhs;
 #pragma unroll
         for (int ct = 0; ct < 2; ++ct) {
             if (ct >= nxt) continue;
@@ -2439,7 +2577,7 @@ __global__ __launch_bounds__(256) void m2l_mrhs_kernel(DevTree T, DevOp O, int f
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int b = LP ? 16 * ct + 4 * lg + e : 16 * ct + 4 * e + lg;  // source node of element e
-                sn[e] = (R)O.nnorm[(size_t)s * nxp + b];
+                sn[e] = (R)Os.nnorm[(size_t)s * nxp + b];
 #pragma unroll
                 for (int rb = 0; rb < 2; ++rb) {
                     // B operand of chunk e: lane (r + 16 g) holds m_s[source node][rhs 16 rb + r]
@@ -2515,6 +2653,150 @@ __global__ __launch_bounds__(256) void m2l_mrhs_kernel(DevTree T, DevOp O, int f
     for (int p = tid; p < nx * nrhs; p += 256) {
         const int a = p / nrhs, r = p % nrhs;
         O.L[(size_t)c * nx * nrhs + p] = part[a * 33 + r];
+    }
+}
+
+template <int KIND, int DK, int PREC>
+__global__ __launch_bounds__(256) void m2l_mrhs_kernel(DevTree T, DevOp O, int first, int nrhs)
+{
+    m2l_mrhs_body<KIND, DK, PREC>(T, O, O, first, nrhs);
+}
+
+template <int KIND, int DK>
+__global__ __launch_bounds__(256) void m2l_mrhs_cross_kernel(DevTree T, DevOp Ot, DevOp Os, int first, int nrhs)
+{
+    m2l_mrhs_body<KIND, DK, 0>(T, Ot, Os, first, nrhs);
+}
+
+template <int KIND>
+void launch_m2l_mrhs_cross_k(const DevTree &T, const DevOp &Ot, const DevOp &Os, int first, int cnt, int nrhs,
+                             hipStream_t st)
+{
+    switch ((T.d + 3) / 4 * 4) {
+#define DWFMM_M2LRC(D) \
+    case D: hipLaunchKernelGGL((m2l_mrhs_cross_kernel<KIND, D>), dim3(cnt), dim3(256), 0, st, T, Ot, Os, first, nrhs); break;
+        DWFMM_M2LRC(4) DWFMM_M2LRC(8) DWFMM_M2LRC(12) DWFMM_M2LRC(16) DWFMM_M2LRC(20) DWFMM_M2LRC(24) DWFMM_M2LRC(28)
+    default:
+        DWFMM_M2LRC(32)
+#undef DWFMM_M2LRC
+    }
+}
+
+// ---------------------------------------------------------------- M2L on FP64 MFMA, large index sets
+// Up to 128 nodes (8 node tiles) and 32 rhs, target and source side separate: the cases the kernels
+// above leave out (n_x > 64 with one rhs, n_x > 32 with several).  One workgroup per target cluster;
+// wave w holds the target node tiles w and w + 4 as the Gram's B operand, so the four waves share
+// every source tile (read from L2, no staging, no barrier) and each local is summed by one lane
+// group in list order.  RB as in the several-rhs nearfield: the kernel tile is the A operand of the
+// apply MFMA; RB = 0 (one rhs) sums on the vector ALU.  Bound by the FP64 pipe; against the general
+// kernel (one thread per coupling entry, S through LDS) at N = 1e5, d = 20, n_x = 97, 25 rhs:
+// 35.8 -> 4.6 ms.
+template <int KIND, int DK, int RB>
+__global__ __launch_bounds__(256) void m2l_wide_kernel(DevTree T, DevOp O, DevOp Os, int first, int nrhs)
+{
+    constexpr int NKC = DK / 4;
+    const int c = first + blockIdx.x;
+    const int nx = O.nx, nxp = O.nxp, nxt = nxp / 16;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, lg = lane >> 4;
+    if (w >= nxt) return;  // no barrier follows
+    const int f0 = T.Fptr[c], f1 = T.Fptr[c + 1];
+    const double inv_ell = 1.0 / O.ell;
+    const bool two = w + 4 < nxt;  // uniform over the wave
+    const double *tnode = O.nodesT + (size_t)c * DK * nxp;
+    double Bt[2][NKC], tn[2], racc[2] = {0.0, 0.0};
+    dbl4 Y[2][RB == 0 ? 1 : RB];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int a = 16 * (two ? w + 4 * u : w) + li;
+#pragma unroll
+        for (int kc = 0; kc < NKC; ++kc) Bt[u][kc] = tnode[(4 * kc + lg) * nxp + a];
+        tn[u] = O.nnorm[(size_t)c * nxp + a];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) Y[u][rb] = dbl4{0.0, 0.0, 0.0, 0.0};
+    }
+    for (int f = f0; f < f1; ++f) {
+        const int s = T.Fsrc[f];
+        const double *snode = Os.nodesT + (size_t)s * DK * nxp;
+        const double *snorm = Os.nnorm + (size_t)s * nxp;
+        const double *ms = Os.M + (size_t)s * nx * nrhs;
+        for (int ct = 0; ct < nxt; ++ct) {
+            double Af[NKC], sn[4], Mq[RB == 0 ? 1 : RB][4];
+#pragma unroll
+            for (int kc = 0; kc < NKC; ++kc) Af[kc] = snode[(4 * kc + lg) * nxp + 16 * ct + li];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int b = 16 * ct + 4 * e + lg;  // source node of element e; padding nodes carry moment 0
+                sn[e] = snorm[b];
+                const int bb = b < nx ? b : nx - 1;
+                if constexpr (RB == 0) {
+                    const double m = ms[bb];
+                    Mq[0][e] = b < nx ? m : 0.0;
+                }
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) {
+                    const int r = 16 * rb + li;
+                    const double m = ms[(size_t)bb * nrhs + (r < nrhs ? r : 0)];
+                    Mq[rb][e] = b < nx && r < nrhs ? m : 0.0;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (u == 1 && !two) break;
+                dbl4 G = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int kc = 0; kc < NKC; ++kc) G = __builtin_amdgcn_mfma_f64_16x16x4f64(Af[kc], Bt[u][kc], G, 0, 0, 0);
+                double Kv[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) Kv[e] = kernel_fast<KIND>(fmax(fma(-2.0, G[e], tn[u] + sn[e]), 0.0), inv_ell);
+                if constexpr (RB == 0) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) racc[u] = fma(Kv[e], Mq[0][e], racc[u]);
+                }
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) Y[u][rb] = __builtin_amdgcn_mfma_f64_16x16x4f64(Kv[e], Mq[rb][e], Y[u][rb], 0, 0, 0);
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        if (u == 1 && !two) break;
+        const int a0 = 16 * (w + 4 * u);
+        if constexpr (RB == 0) {
+            double acc = racc[u];  // lane (a + 16 g): target node a, source nodes 4 e + g
+            acc += __shfl_xor(acc, 16, 64);
+            acc += __shfl_xor(acc, 32, 64);
+            if (lg == 0 && a0 + li < nx) O.L[(size_t)c * nx + a0 + li] = acc;
+        } else {
+            // element v of lane (r + 16 g): target node 4 v + g, rhs r
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int a = a0 + 4 * v + lg, r = 16 * rb + li;
+                    if (a < nx && r < nrhs) O.L[((size_t)c * nx + a) * nrhs + r] = Y[u][rb][v];
+                }
+        }
+    }
+}
+
+template <int KIND>
+void launch_m2l_wide_k(const DevTree &T, const DevOp &Ot, const DevOp &Os, int first, int cnt, int nrhs, hipStream_t st)
+{
+    const int rb = nrhs == 1 ? 0 : nrhs <= 16 ? 1 : 2;
+    switch ((T.d + 3) / 4 * 4) {
+#define DWFMM_M2LW(D)                                                                                                  \
+    case D:                                                                                                            \
+        if (rb == 0) hipLaunchKernelGGL((m2l_wide_kernel<KIND, D, 0>), dim3(cnt), dim3(256), 0, st, T, Ot, Os, first, nrhs); \
+        else if (rb == 1) hipLaunchKernelGGL((m2l_wide_kernel<KIND, D, 1>), dim3(cnt), dim3(256), 0, st, T, Ot, Os, first, nrhs); \
+        else hipLaunchKernelGGL((m2l_wide_kernel<KIND, D, 2>), dim3(cnt), dim3(256), 0, st, T, Ot, Os, first, nrhs);    \
+        break;
+        DWFMM_M2LW(4) DWFMM_M2LW(8) DWFMM_M2LW(12) DWFMM_M2LW(16) DWFMM_M2LW(20) DWFMM_M2LW(24) DWFMM_M2LW(28)
+    default:
+        DWFMM_M2LW(32)
+#undef DWFMM_M2LW
     }
 }
 
@@ -3078,9 +3360,11 @@ __global__ __launch_bounds__(256) void cg_item_kernel(const CgItem *__restrict__
 
 }  // namespace
 
-// The library compiles this file twice, in parallel: DWFMM_KERNELS_PART 1 holds the
-// single-problem entry points, 2 the batched ones; each instantiates only the kernel
-// templates it launches.  Without the macro both parts are compiled.
+// The library compiles this file in parallel parts: DWFMM_KERNELS_PART 1 holds the
+// single-problem matvec and CG, 2 the batched entry points, 3 evaluation, the nearfield of leaves
+// above kSymLeaf points and the coupling of large index sets, 4 the reduced-precision several-rhs
+// nearfield and the several-rhs coupling; each instantiates only the kernel templates it launches.
+// Without the macro every part is compiled.
 #if !defined(DWFMM_KERNELS_PART) || DWFMM_KERNELS_PART == 1
 hipError_t launch_basis(const DevTree &T, int nx, const double *clo, const double *csc, const double *coff,
                         const int32_t *lidx, int nnz_max, const double *Vinv, int nleg, const int32_t *leg_axis,
@@ -3104,13 +3388,9 @@ hipError_t launch_matvec(const DevTree &T, const DevOp &O, const double *x, doub
     // MFMA nearfield for several rhs (LDS of the FP64 kernel: at most 66 KB, at d <= 28 with two
     // 16-wide rhs tiles; gfx950 gives a workgroup up to 160 KB)
     const int dk = (T.d + 3) / 4 * 4;
-    const bool mrhs = nrhs > 1 && O.kind <= 2 && T.max_leaf <= kSymLeaf && dk <= 32 && !(dk > 28 && nrhs > 16);
-    if (nrhs > 1 && T.max_leaf * nrhs <= 4096)
-        hipLaunchKernelGGL(p2m_multi_kernel, dim3(T.nleaf), dim3(256), sizeof(double) * T.max_leaf * nrhs, main_st, T,
-                           O, x, nrhs, far);
-    else
-        hipLaunchKernelGGL(p2m_kernel, dim3(T.nleaf), dim3(256), sizeof(double) * T.max_leaf, main_st, T, O, x, nrhs,
-                           far);
+    // (leaves above kSymLeaf points: FP64 in every precision mode, one rhs too)
+    const bool mrhs = (nrhs > 1 || T.max_leaf > kSymLeaf) && O.kind <= 2 && dk <= 32 && !(dk > 28 && nrhs > 16);
+    launch_p2m(T, O, x, nrhs, far, main_st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // the symmetric nearfield does not read the locals, nor does the several-rhs one when its L2P
@@ -3133,17 +3413,12 @@ hipError_t launch_matvec(const DevTree &T, const DevOp &O, const double *x, doub
         if (timer) (void)hipEventRecord(timer->m2l_start, st);
         const bool mfma = nrhs == 1 && O.kind <= 2 && T.d <= 32 && O.nxp <= 64 && O.nodesT && O.nnorm;
         const bool mfma_r = nrhs > 1 && O.kind <= 2 && T.d <= 32 && O.nxp <= 32 && O.nodesT && O.nnorm;
+        // larger index sets of radial kernels: FP64 in every precision mode
+        const bool wide = !mfma && !mfma_r && O.kind <= 2 && T.d <= 32 && O.nodesT && O.nnorm;
         if (mfma_r) {
-#define DWFMM_M2LR_PREC(K)                                                      \
-    (precision == 0   ? launch_m2l_mrhs_k<K, 0>(T, O, first, cnt, nrhs, st)     \
-     : precision == 1 ? launch_m2l_mrhs_k<K, 1>(T, O, first, cnt, nrhs, st)     \
-                      : launch_m2l_mrhs_k<K, 2>(T, O, first, cnt, nrhs, st))
-            switch (O.kind) {
-            case 0: DWFMM_M2LR_PREC(0); break;
-            case 1: DWFMM_M2LR_PREC(1); break;
-            default: DWFMM_M2LR_PREC(2); break;
-            }
-#undef DWFMM_M2LR_PREC
+            if ((e = launch_m2l_mrhs(T, O, first, cnt, nrhs, precision, st)) != hipSuccess) return e;
+        } else if (wide) {
+            if ((e = launch_m2l_wide(T, O, O, first, cnt, nrhs, st)) != hipSuccess) return e;
         } else if (mfma && precision != 0) {
             switch (O.kind) {
             case 0: launch_m2l32_k<0>(T, O, first, cnt, st); break;
@@ -3197,7 +3472,9 @@ hipError_t launch_matvec(const DevTree &T, const DevOp &O, const double *x, doub
     if (mrhs) {
         // split: the nearfield kernel writes the near part only; L2P adds the farfield after the join
         const int nfar = split ? 0 : far;
-        if (precision == 0) {
+        if (T.max_leaf > kSymLeaf) {
+            e = launch_pieces(T, O, T, O.xt, y, nrhs, near, nfar, st);
+        } else if (precision == 0) {
             switch (O.kind) {
             case 0: e = launch_mrhs_k<0>(T, O, y, nrhs, near, nfar, st); break;
             case 1:
@@ -3206,35 +3483,8 @@ hipError_t launch_matvec(const DevTree &T, const DevOp &O, const double *x, doub
                 break;
             default: e = launch_mrhs_k<2>(T, O, y, nrhs, near, nfar, st); break;
             }
-        } else if (precision == 1) {
-            switch (O.kind) {
-            case 0: e = launch_mrhs_lp_k<0, false>(T, O, y, nrhs, near, nfar, st); break;
-            case 1:
-                e = O.gauss_split32 ? launch_mrhs_lp_k<kGaussSplit, false>(T, O, y, nrhs, near, nfar, st)
-                                    : launch_mrhs_lp_k<1, false>(T, O, y, nrhs, near, nfar, st);
-                break;
-            default: e = launch_mrhs_lp_k<2, false>(T, O, y, nrhs, near, nfar, st); break;
-            }
         } else {
-            if (near && !O.xtb) return hipErrorInvalidValue;  // the BF16 charges are staged from xtb
-            // BF16 tile cache: the first nearfield launch writes the tiles, later ones read them (not
-            // inside a graph capture, whose launches run later than the host flag would say)
-            DevOp Oc = O;
-            Oc.near_cache_mode = 0;
-            if (O.near_tiles && near) {
-                hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-                if ((e = hipStreamIsCapturing(st, &cs)) != hipSuccess) return e;
-                if (cs == hipStreamCaptureStatusNone) Oc.near_cache_mode = *O.near_filled ? 2 : 1;
-            }
-            switch (O.kind) {
-            case 0: e = launch_mrhs_lp_k<0, true>(T, Oc, y, nrhs, near, nfar, st); break;
-            case 1:
-                e = O.gauss_split32 ? launch_mrhs_lp_k<kGaussSplit, true>(T, Oc, y, nrhs, near, nfar, st)
-                                    : launch_mrhs_lp_k<1, true>(T, Oc, y, nrhs, near, nfar, st);
-                break;
-            default: e = launch_mrhs_lp_k<2, true>(T, Oc, y, nrhs, near, nfar, st); break;
-            }
-            if (e == hipSuccess && Oc.near_cache_mode == 1) *O.near_filled = 1;
+            e = launch_mrhs_lp(T, O, y, nrhs, near, nfar, precision, st);
         }
         if (timer) (void)hipEventRecord(timer->p2p_stop, st);
         if (e != hipSuccess || !split) return e;
@@ -3314,7 +3564,30 @@ hipError_t launch_batch_matvec(const BatchPlan &P, hipStream_t st, const StreamF
 
 #endif
 
-#if !defined(DWFMM_KERNELS_PART) || DWFMM_KERNELS_PART == 1
+#if !defined(DWFMM_KERNELS_PART) || DWFMM_KERNELS_PART == 3
+hipError_t launch_m2l_wide(const DevTree &T, const DevOp &Ot, const DevOp &Os, int first, int cnt, int nrhs,
+                           hipStream_t st)
+{
+    switch (Os.kind) {
+    case 0: launch_m2l_wide_k<0>(T, Ot, Os, first, cnt, nrhs, st); break;
+    case 1: launch_m2l_wide_k<1>(T, Ot, Os, first, cnt, nrhs, st); break;
+    default: launch_m2l_wide_k<2>(T, Ot, Os, first, cnt, nrhs, st); break;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_pieces(const DevTree &T, const DevOp &O, const DevTree &Ts, const double *xs, double *y, int nrhs,
+                         int near, int far, hipStream_t st)
+{
+    switch (O.kind) {
+    case 0: return launch_pieces_k<0>(T, O, Ts, xs, y, nrhs, near, far, st);
+    case 1:
+        return O.gauss_split ? launch_pieces_k<kGaussSplit>(T, O, Ts, xs, y, nrhs, near, far, st)
+                             : launch_pieces_k<1>(T, O, Ts, xs, y, nrhs, near, far, st);
+    default: return launch_pieces_k<2>(T, O, Ts, xs, y, nrhs, near, far, st);
+    }
+}
+
 hipError_t launch_eval(const DevTree &Tt, const DevOp &Ot, const DevTree &Ts, const DevOp &Os, const double *x,
                        double *y, int nrhs, hipStream_t st)
 {
@@ -3322,21 +3595,29 @@ hipError_t launch_eval(const DevTree &Tt, const DevOp &Ot, const DevTree &Ts, co
         return hipErrorInvalidValue;
     const int far = Tt.min_far_level <= Tt.J;
     // source side: charges into tree order and, if needed, moments up to the first cross-farfield level
-    hipLaunchKernelGGL(p2m_kernel, dim3(Ts.nleaf), dim3(256), sizeof(double) * Ts.max_leaf, st, Ts, Os, x, nrhs, far);
+    launch_p2m(Ts, Os, x, nrhs, far, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    const bool radial = Os.kind <= 2 && Tt.d <= 32;
     if (far) {
         for (int j = Ts.J - 1; j >= Tt.min_far_level; --j)
             hipLaunchKernelGGL(m2m_kernel, dim3(1 << j), dim3(64), 0, st, Ts, Os, (1 << j) - 1, nrhs);
         const int first = (1 << Tt.min_far_level) - 1;
         const int cnt = Tt.ncl - first;
-        // one rhs, radial kernels, d <= 32, n_x <= 64: node-pair distances on FP64 MFMA
-        const bool mfma = nrhs == 1 && Os.kind <= 2 && Tt.d <= 32 && Os.nxp <= 64 && Ot.nodesT && Ot.nnorm &&
-                          Os.nodesT && Os.nnorm;
-        if (mfma) switch (Os.kind) {
+        // radial kernels, d <= 32: node-pair distances on FP64 MFMA
+        const bool mfma = radial && Ot.nodesT && Ot.nnorm && Os.nodesT && Os.nnorm;
+        if (mfma && nrhs == 1 && Os.nxp <= 64) switch (Os.kind) {
         case 0: launch_m2l_cross_mfma_k<0>(Tt, Ot, Os, first, cnt, st); break;
         case 1: launch_m2l_cross_mfma_k<1>(Tt, Ot, Os, first, cnt, st); break;
         default: launch_m2l_cross_mfma_k<2>(Tt, Ot, Os, first, cnt, st); break;
+        }
+        else if (mfma && nrhs > 1 && Os.nxp <= 32) switch (Os.kind) {
+        case 0: launch_m2l_mrhs_cross_k<0>(Tt, Ot, Os, first, cnt, nrhs, st); break;
+        case 1: launch_m2l_mrhs_cross_k<1>(Tt, Ot, Os, first, cnt, nrhs, st); break;
+        default: launch_m2l_mrhs_cross_k<2>(Tt, Ot, Os, first, cnt, nrhs, st); break;
+        }
+        else if (mfma) {
+            if ((e = launch_m2l_wide(Tt, Ot, Os, first, cnt, nrhs, st)) != hipSuccess) return e;
         }
         else switch (Os.kind) {
         case 0: hipLaunchKernelGGL(m2l_cross_kernel<0>, dim3(cnt), dim3(256), 0, st, Tt, Ot, Os, first, nrhs); break;
@@ -3349,7 +3630,7 @@ hipError_t launch_eval(const DevTree &Tt, const DevOp &Ot, const DevTree &Ts, co
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     // one rhs, radial kernels, target leaves of at most kSymLeaf points, d <= 32: MFMA nearfield
-    if (nrhs == 1 && Os.kind <= 2 && Tt.max_leaf <= kSymLeaf && Tt.dpad <= 32) {
+    if (nrhs == 1 && radial && Tt.max_leaf <= kSymLeaf) {
         switch (Os.kind) {
         case 0: return launch_cross_mfma_k<0>(Tt, Ot, Ts, Os.xt, y, far, st);
         case 1:
@@ -3358,6 +3639,8 @@ hipError_t launch_eval(const DevTree &Tt, const DevOp &Ot, const DevTree &Ts, co
         default: return launch_cross_mfma_k<2>(Tt, Ot, Ts, Os.xt, y, far, st);
         }
     }
+    // several rhs or larger leaves (66 KB of LDS at most, as the several-rhs nearfield)
+    if (radial && !(Tt.dpad > 28 && nrhs > 16)) return launch_pieces(Tt, Ot, Ts, Os.xt, y, nrhs, 1, far, st);
     switch (Os.kind) {
     case 0: return launch_p2p_cross_k<0>(Tt, Ot, Ts, Os.xt, y, nrhs, far, st);
     case 1: return launch_p2p_cross_k<1>(Tt, Ot, Ts, Os.xt, y, nrhs, far, st);
@@ -3366,6 +3649,62 @@ hipError_t launch_eval(const DevTree &Tt, const DevOp &Ot, const DevTree &Ts, co
     }
 }
 
+#endif
+
+#if !defined(DWFMM_KERNELS_PART) || DWFMM_KERNELS_PART == 4
+hipError_t launch_m2l_mrhs(const DevTree &T, const DevOp &O, int first, int cnt, int nrhs, int precision, hipStream_t st)
+{
+#define DWFMM_M2LR_PREC(K)                                                  \
+    (precision == 0   ? launch_m2l_mrhs_k<K, 0>(T, O, first, cnt, nrhs, st) \
+     : precision == 1 ? launch_m2l_mrhs_k<K, 1>(T, O, first, cnt, nrhs, st) \
+                      : launch_m2l_mrhs_k<K, 2>(T, O, first, cnt, nrhs, st))
+    switch (O.kind) {
+    case 0: DWFMM_M2LR_PREC(0); break;
+    case 1: DWFMM_M2LR_PREC(1); break;
+    default: DWFMM_M2LR_PREC(2); break;
+    }
+#undef DWFMM_M2LR_PREC
+    return hipGetLastError();
+}
+
+hipError_t launch_mrhs_lp(const DevTree &T, const DevOp &O, double *y, int nrhs, int near, int far, int precision,
+                          hipStream_t st)
+{
+    hipError_t e;
+    if (precision == 1) {
+        switch (O.kind) {
+        case 0: return launch_mrhs_lp_k<0, false>(T, O, y, nrhs, near, far, st);
+        case 1:
+            return O.gauss_split32 ? launch_mrhs_lp_k<kGaussSplit, false>(T, O, y, nrhs, near, far, st)
+                                   : launch_mrhs_lp_k<1, false>(T, O, y, nrhs, near, far, st);
+        default: return launch_mrhs_lp_k<2, false>(T, O, y, nrhs, near, far, st);
+        }
+    }
+    if (near && !O.xtb) return hipErrorInvalidValue;  // the BF16 charges are staged from xtb
+    // BF16 tile cache: the first nearfield launch writes the tiles, later ones read them (not
+    // inside a graph capture, whose launches run later than the host flag would say)
+    DevOp Oc = O;
+    Oc.near_cache_mode = 0;
+    if (O.near_tiles && near) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if ((e = hipStreamIsCapturing(st, &cs)) != hipSuccess) return e;
+        if (cs == hipStreamCaptureStatusNone) Oc.near_cache_mode = *O.near_filled ? 2 : 1;
+    }
+    switch (O.kind) {
+    case 0: e = launch_mrhs_lp_k<0, true>(T, Oc, y, nrhs, near, far, st); break;
+    case 1:
+        e = O.gauss_split32 ? launch_mrhs_lp_k<kGaussSplit, true>(T, Oc, y, nrhs, near, far, st)
+                            : launch_mrhs_lp_k<1, true>(T, Oc, y, nrhs, near, far, st);
+        break;
+    default: e = launch_mrhs_lp_k<2, true>(T, Oc, y, nrhs, near, far, st); break;
+    }
+    if (e == hipSuccess && Oc.near_cache_mode == 1) *O.near_filled = 1;
+    return e;
+}
+
+#endif
+
+#if !defined(DWFMM_KERNELS_PART) || DWFMM_KERNELS_PART == 1
 hipError_t launch_dot(const double *a, const double *b, int n, int nrhs, double *partial, double *out,
                       hipStream_t stream)
 {
