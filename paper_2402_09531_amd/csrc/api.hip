@@ -1333,6 +1333,7 @@ static dwfmm_status batch_build(const dwfmm_op *ops, int32_t count, int32_t flag
     if (!out) return fail(DWFMM_E_INVALID, "out is NULL");
     *out = nullptr;
     if (!ops || count < 1) return fail(DWFMM_E_INVALID, "ops is NULL or count < 1");
+    if (count >= 1 << kXferDepthBit) return fail(DWFMM_E_INVALID, "too many operators");
     for (int i = 0; i < count; ++i)
         if (!ops[i]) return fail(DWFMM_E_INVALID, "ops contains NULL");
     const int forced = (flags >> 4) & 7;
@@ -1368,25 +1369,27 @@ static dwfmm_status batch_build(const dwfmm_op *ops, int32_t count, int32_t flag
     for (int it = 0; it < (int)b->items.size(); ++it)
         for (int l = 0; l < b->items[it].T.nleaf; ++l) work.push_back(make_int2(it, l));
     P.leaf_cnt = (int)work.size();
-    int maxJ = 0;
-    for (auto &it : b->items) maxJ = std::max(maxJ, it.T.J);
-    for (int j = maxJ - 1; j >= 0; --j) {
-        const int off = (int)work.size();
-        for (int it = 0; it < (int)b->items.size(); ++it) {
+    // M2M and L2L: the k-th launch holds the k-th level group of every problem
+    for (const bool up : {true, false}) {
+        std::vector<std::vector<XferGroup>> groups(b->items.size());
+        size_t most = 0;
+        for (size_t it = 0; it < b->items.size(); ++it) {
             const BatchItem &I = b->items[it];
-            if (!I.far || j < I.T.min_far_level || j >= I.T.J) continue;
-            for (int c = (1 << j) - 1; c < (1 << (j + 1)) - 1; ++c) work.push_back(make_int2(it, c));
+            if (!I.far) continue;
+            groups[it] = up ? xfer_groups(true, I.O.nx, 1, I.T.min_far_level, I.T.J - 1)
+                            : xfer_groups(false, I.O.nx, 1, I.T.min_far_level + 1, I.T.J);
+            most = std::max(most, groups[it].size());
         }
-        if ((int)work.size() > off) P.m2m.push_back({off, (int)work.size() - off});
-    }
-    for (int j = 1; j <= maxJ; ++j) {
-        const int off = (int)work.size();
-        for (int it = 0; it < (int)b->items.size(); ++it) {
-            const BatchItem &I = b->items[it];
-            if (!I.far || j < I.T.min_far_level + 1 || j > I.T.J) continue;
-            for (int c = (1 << j) - 1; c < (1 << (j + 1)) - 1; ++c) work.push_back(make_int2(it, c));
+        for (size_t k = 0; k < most; ++k) {
+            const int off = (int)work.size();
+            for (size_t it = 0; it < groups.size(); ++it) {
+                if (k >= groups[it].size()) continue;
+                const XferGroup g = groups[it][k];
+                for (int c = (1 << g.root) - 1; c < (1 << (g.root + 1)) - 1; ++c)
+                    work.push_back(make_int2((int)it | g.depth << kXferDepthBit, c));
+            }
+            (up ? P.m2m : P.l2l).push_back({off, (int)work.size() - off});
         }
-        if ((int)work.size() > off) P.l2l.push_back({off, (int)work.size() - off});
     }
     auto key = [&](const BatchItem &I, bool far_list) {
         // the FP64 nearfield of a split Gaussian runs its own kernel variant (kind 4), the FP64

@@ -135,6 +135,41 @@ struct BatchItem {
     int precision;  // 0 FP64, 1/2 FP32 nearfield and coupling
 };
 
+// M2M (up) and L2L passes: consecutive tree levels run by one launch, one workgroup per cluster of
+// level `root`, each over the `depth` levels of its subtree (M2M: the deepest first).
+struct XferGroup {
+    int root, depth;
+};
+// The launches of M2M over levels hi, ..., lo (up) or L2L over levels lo, ..., hi, in order.  A
+// launch costs about 5 us however little it does and a level inside one about 1 us, so levels are
+// joined while a workgroup's subtree stays within 4000 cycles of products (1.7 us), or where the
+// launch has 2048 workgroups (8 per CU) anyhow.  Cycles of one CU per cluster: one rhs about 24
+// terms a cycle over its threads; several rhs 64 per FP64 MFMA on four SIMDs.
+inline std::vector<XferGroup> xfer_groups(bool up, int nx, int nrhs, int lo, int hi)
+{
+    const int64_t src = up ? 2 : 1, nxt = (nx + 15) / 16, rb = (nrhs + 15) / 16;
+    const int64_t cyc = nrhs == 1 ? std::max<int64_t>(1, src * nx * nx / 24) : src * nxt * rb * ((nx + 3) / 4) * 16;
+    auto join = [&](int root, int depth) { return cyc * (((int64_t)1 << depth) - 1) <= 4000 || root >= 11; };
+    std::vector<XferGroup> g;
+    if (up) {
+        for (int j = hi; j >= lo;) {
+            int r = j;
+            while (r > lo && join(r - 1, j - r + 2)) --r;
+            g.push_back({r, j - r + 1});
+            j = r - 1;
+        }
+    } else {
+        for (int j = lo; j <= hi;) {
+            int depth = 1;
+            while (j + depth <= hi && join(j, depth + 1)) ++depth;
+            g.push_back({j, depth});
+            j += depth;
+        }
+    }
+    return g;
+}
+constexpr int kXferDepthBit = 24;
+
 // One launch of a templated kernel over a slice of the work list.  wpc (M2L only): waves per
 // target cluster, 4, 2 or 1; every choice gives bitwise the same locals.
 struct BatchLaunch {
@@ -152,7 +187,8 @@ struct BatchPlan {
     double *const *ys = nullptr;
     const int2 *work = nullptr;
     int leaf_off = 0, leaf_cnt = 0;
-    std::vector<std::pair<int, int>> m2m, l2l;  // (offset, count) per level in launch order
+    // (offset, count) per launch: entries (item | depth << kXferDepthBit, root cluster)
+    std::vector<std::pair<int, int>> m2m, l2l;
     std::vector<BatchLaunch> m2l, p2p;
 };
 

@@ -283,25 +283,134 @@ void launch_p2m(const DevTree &T, const DevOp &O, const double *x, int nrhs, int
         hipLaunchKernelGGL(p2m_kernel, dim3(T.nleaf), dim3(256), sizeof(double) * T.max_leaf, st, T, O, x, nrhs, do_far);
 }
 
-// ---------------------------------------------------------------- M2M, one level
-__device__ __forceinline__ void m2m_body(const DevTree &T, const DevOp &O, int c, int nrhs)
+// ---------------------------------------------------------------- M2M and L2L
+// One workgroup runs the subtree below (M2M: ending at; L2L: starting from) one cluster, level by
+// level with a barrier between levels, so a pass takes a launch per group of levels instead of one
+// per level; xfer_groups picks the groups.  A pass is a chain of small steps: its time is the
+// launches and the latency of each level's loads, and for many nodes and rhs the products.
+//   one rhs       a thread per (cluster, node), terms in node order
+//   several rhs   a wave per (cluster, 16 nodes): E m on FP64 MFMA, the rhs as columns
+// Against one launch per level, 64 threads per cluster, a thread per output (M2M / L2L, each launch
+// beside the nearfield): N = 1e5, n_x = 97, 25 rhs 8 x 1780 / 8 x 600 us -> 8 x 258 / 8 x 70 us;
+// N = 2e5, n_x = 15, 32 rhs 9 x 54 / 9 x 34 -> 3 x 96 / 2 x 40; N = 4096, n_x = 11, one rhs (alone)
+// 4 x 5.1 / 4 x 4.0 -> 8.5 / 6.5.
+// m_c[a] = sum over the children ch of sum_b E_ch[b][a] m_ch[b]
+__device__ __forceinline__ void m2m_node(const DevOp &O, int c, int a)
 {
     const int nx = O.nx;
-    for (int p = threadIdx.x; p < nx * nrhs; p += blockDim.x) {
-        const int a = p / nrhs, r = p % nrhs;
-        double s = 0.0;
-        for (int ch = 2 * c + 1; ch <= 2 * c + 2; ++ch) {
-            const double *E = O.E + (size_t)ch * nx * nx;
-            const double *m = O.M + (size_t)ch * nx * nrhs;
-            for (int b = 0; b < nx; ++b) s += E[b * nx + a] * m[b * nrhs + r];
+    double s = 0.0;
+    for (int ch = 2 * c + 1; ch <= 2 * c + 2; ++ch) {
+        const double *E = O.E + (size_t)ch * nx * nx + a;
+        const double *m = O.M + (size_t)ch * nx;
+#pragma unroll 8
+        for (int b = 0; b < nx; ++b) s += E[b * nx] * m[b];
+    }
+    O.M[(size_t)c * nx + a] = s;
+}
+
+// l_c[a] += sum_b E_c[a][b] l_parent[b]
+__device__ __forceinline__ void l2l_node(const DevOp &O, int c, int a)
+{
+    const int nx = O.nx;
+    const double *E = O.E + ((size_t)c * nx + a) * nx;
+    const double *lp = O.L + (size_t)((c - 1) / 2) * nx;
+    double s = 0.0;
+#pragma unroll 8
+    for (int b = 0; b < nx; ++b) s += E[b] * lp[b];
+    O.L[(size_t)c * nx + a] += s;
+}
+
+// One 16-node tile of the same, all rhs (RB 16-wide rhs tiles), by one wave: the MFMA's k runs over
+// the source nodes, padding nodes are zero in both operands.
+template <int RB, bool UP>
+__device__ __forceinline__ void xfer_tile(const DevOp &O, int c, int rt, int nrhs, int li, int lg)
+{
+    const int nx = O.nx, a = 16 * rt + li, aa = min(a, nx - 1);
+    dbl4 Y[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) Y[rb] = dbl4{0.0, 0.0, 0.0, 0.0};
+    for (int h = 0; h < (UP ? 2 : 1); ++h) {
+        const int ch = UP ? 2 * c + 1 + h : c, sc = UP ? ch : (c - 1) / 2;
+        const double *E = O.E + (size_t)ch * nx * nx;
+        const double *m = (UP ? O.M : O.L) + (size_t)sc * nx * nrhs;
+        // 16 source nodes at a time, their loads issued together
+        for (int b0 = 0; b0 < nx; b0 += 16) {
+            double ev[4], mv[4][RB];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int b = b0 + 4 * k + lg, bb = min(b, nx - 1);
+                ev[k] = UP ? E[bb * nx + aa] : E[aa * nx + bb];
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) mv[k][rb] = m[(size_t)bb * nrhs + min(16 * rb + li, nrhs - 1)];
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (b0 + 4 * k >= nx) break;  // uniform
+                const bool ok = b0 + 4 * k + lg < nx;
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb)
+                    Y[rb] = __builtin_amdgcn_mfma_f64_16x16x4f64(ok ? ev[k] : 0.0, ok ? mv[k][rb] : 0.0, Y[rb], 0, 0, 0);
+            }
         }
-        O.M[((size_t)c * nx + a) * nrhs + r] = s;
+    }
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int ao = 16 * rt + 4 * v + lg, r = 16 * rb + li;
+            if (ao >= nx || r >= nrhs) continue;
+            if constexpr (UP) O.M[((size_t)c * nx + ao) * nrhs + r] = Y[rb][v];
+            else O.L[((size_t)c * nx + ao) * nrhs + r] += Y[rb][v];
+        }
+}
+
+// The clusters `lev` levels below root: ids [((root + 1) << lev) - 1, + (1 << lev)).
+template <int RB, bool UP>
+__device__ __forceinline__ void xfer_level(const DevOp &O, int root, int lev, int nrhs)
+{
+    const int first = ((root + 1) << lev) - 1, cnt = 1 << lev;
+    if constexpr (RB == 0) {
+        for (int p = threadIdx.x; p < cnt * O.nx; p += blockDim.x) {
+            const int i = p / O.nx, a = p - i * O.nx;
+            if constexpr (UP) m2m_node(O, first + i, a);
+            else l2l_node(O, first + i, a);
+        }
+    } else {
+        const int nxt = (O.nx + 15) / 16, lane = threadIdx.x & 63;
+        for (int p = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); p < cnt * nxt; p += blockDim.x >> 6) {
+            const int i = p / nxt;
+            xfer_tile<RB, UP>(O, first + i, p - i * nxt, nrhs, lane & 15, lane >> 4);
+        }
     }
 }
 
-__global__ __launch_bounds__(64) void m2m_kernel(DevTree T, DevOp O, int first, int nrhs)
+template <int RB, bool UP>
+__device__ __forceinline__ void xfer_body(const DevOp &O, int root, int depth, int nrhs)
 {
-    m2m_body(T, O, first + blockIdx.x, nrhs);
+    for (int k = 0; k < depth; ++k) {
+        if (k) __syncthreads();  // the level before is written (and visible to the workgroup)
+        xfer_level<RB, UP>(O, root, UP ? depth - 1 - k : k, nrhs);
+    }
+}
+
+template <int RB, bool UP>
+__global__ __launch_bounds__(256) void xfer_kernel(DevOp O, int first, int depth, int nrhs)
+{
+    xfer_body<RB, UP>(O, first + blockIdx.x, depth, nrhs);
+}
+
+// M2M over levels hi, hi - 1, ..., lo (UP) or L2L over levels lo, ..., hi, at most one launch per
+// group of xfer_groups.
+template <bool UP>
+void launch_xfer(const DevOp &O, int lo, int hi, int nrhs, hipStream_t st)
+{
+    for (const XferGroup &g : xfer_groups(UP, O.nx, nrhs, lo, hi)) {
+        const dim3 grid(1 << g.root), b(256);
+        const int first = (1 << g.root) - 1;
+        if (nrhs == 1) hipLaunchKernelGGL((xfer_kernel<0, UP>), grid, b, 0, st, O, first, g.depth, nrhs);
+        else if (nrhs <= 16) hipLaunchKernelGGL((xfer_kernel<1, UP>), grid, b, 0, st, O, first, g.depth, nrhs);
+        else hipLaunchKernelGGL((xfer_kernel<2, UP>), grid, b, 0, st, O, first, g.depth, nrhs);
+    }
 }
 
 // ---------------------------------------------------------------- M2L, all farfield levels at once
@@ -530,26 +639,6 @@ void launch_m2l_mfma_k(const DevTree &T, const DevOp &O, int first, int cnt, hip
     case 28: launch_m2l_mfma_d<KIND, 28>(T, O, first, cnt, st); break;
     default: launch_m2l_mfma_d<KIND, 32>(T, O, first, cnt, st); break;
     }
-}
-
-// ---------------------------------------------------------------- L2L, one level
-__device__ __forceinline__ void l2l_body(const DevTree &T, const DevOp &O, int c, int nrhs)
-{
-    const int par = (c - 1) / 2;
-    const int nx = O.nx;
-    const double *E = O.E + (size_t)c * nx * nx;
-    const double *lp = O.L + (size_t)par * nx * nrhs;
-    for (int p = threadIdx.x; p < nx * nrhs; p += blockDim.x) {
-        const int a = p / nrhs, r = p % nrhs;
-        double s = 0.0;
-        for (int b = 0; b < nx; ++b) s += E[a * nx + b] * lp[b * nrhs + r];
-        O.L[((size_t)c * nx + a) * nrhs + r] += s;
-    }
-}
-
-__global__ __launch_bounds__(64) void l2l_kernel(DevTree T, DevOp O, int first, int nrhs)
-{
-    l2l_body(T, O, first + blockIdx.x, nrhs);
 }
 
 // ---------------------------------------------------------------- P2P + L2P + scatter to original order
@@ -2932,18 +3021,19 @@ __global__ __launch_bounds__(256) void p2m_batch_kernel(const BatchItem *items, 
     p2m_body(B.T, B.O, wk.y, xs[wk.x], 1, B.far, xl);
 }
 
-__global__ __launch_bounds__(64) void m2m_batch_kernel(const BatchItem *items, const int2 *work)
+// (a work entry is a subtree root, its depth in the item's bits from kXferDepthBit)
+__global__ __launch_bounds__(256) void m2m_batch_kernel(const BatchItem *items, const int2 *work)
 {
     const int2 wk = work[blockIdx.x];
     if (wk.x < 0) return;
-    m2m_body(items[wk.x].T, items[wk.x].O, wk.y, 1);
+    xfer_body<0, true>(items[wk.x & ((1 << kXferDepthBit) - 1)].O, wk.y, wk.x >> kXferDepthBit, 1);
 }
 
-__global__ __launch_bounds__(64) void l2l_batch_kernel(const BatchItem *items, const int2 *work)
+__global__ __launch_bounds__(256) void l2l_batch_kernel(const BatchItem *items, const int2 *work)
 {
     const int2 wk = work[blockIdx.x];
     if (wk.x < 0) return;
-    l2l_body(items[wk.x].T, items[wk.x].O, wk.y, 1);
+    xfer_body<0, false>(items[wk.x & ((1 << kXferDepthBit) - 1)].O, wk.y, wk.x >> kXferDepthBit, 1);
 }
 
 // 4 / WPC clusters of the work list per workgroup and pass; slots past the end or on padding
@@ -3406,8 +3496,7 @@ hipError_t launch_matvec(const DevTree &T, const DevOp &O, const double *x, doub
         st = fork->side;
     }
     if (far) {
-        for (int j = T.J - 1; j >= T.min_far_level; --j)
-            hipLaunchKernelGGL(m2m_kernel, dim3(1 << j), dim3(64), 0, st, T, O, (1 << j) - 1, nrhs);
+        launch_xfer<true>(O, T.min_far_level, T.J - 1, nrhs, st);
         const int first = (1 << T.min_far_level) - 1;
         const int cnt = T.ncl - first;
         if (timer) (void)hipEventRecord(timer->m2l_start, st);
@@ -3440,8 +3529,7 @@ hipError_t launch_matvec(const DevTree &T, const DevOp &O, const double *x, doub
             }
         }
         if (timer) (void)hipEventRecord(timer->m2l_stop, st);
-        for (int j = T.min_far_level + 1; j <= T.J; ++j)
-            hipLaunchKernelGGL(l2l_kernel, dim3(1 << j), dim3(64), 0, st, T, O, (1 << j) - 1, nrhs);
+        launch_xfer<false>(O, T.min_far_level + 1, T.J, nrhs, st);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         if (split && (e = hipEventRecord(fork->joined, fork->side)) != hipSuccess) return e;
@@ -3531,10 +3619,10 @@ hipError_t launch_batch_matvec(const BatchPlan &P, hipStream_t st, const StreamF
         fs = fork->side;
     }
     for (auto &lv : P.m2m)
-        hipLaunchKernelGGL(m2m_batch_kernel, dim3(lv.second), dim3(64), 0, fs, P.items, P.work + lv.first);
+        hipLaunchKernelGGL(m2m_batch_kernel, dim3(lv.second), dim3(256), 0, fs, P.items, P.work + lv.first);
     for (auto &L : P.m2l) (void)launch_batch_m2l(P, L, fs);
     for (auto &lv : P.l2l)
-        hipLaunchKernelGGL(l2l_batch_kernel, dim3(lv.second), dim3(64), 0, fs, P.items, P.work + lv.first);
+        hipLaunchKernelGGL(l2l_batch_kernel, dim3(lv.second), dim3(256), 0, fs, P.items, P.work + lv.first);
     if (forked) {
         hipError_t e = hipEventRecord(fork->joined, fs);
         if (e != hipSuccess) return e;
@@ -3600,8 +3688,7 @@ hipError_t launch_eval(const DevTree &Tt, const DevOp &Ot, const DevTree &Ts, co
     if (e != hipSuccess) return e;
     const bool radial = Os.kind <= 2 && Tt.d <= 32;
     if (far) {
-        for (int j = Ts.J - 1; j >= Tt.min_far_level; --j)
-            hipLaunchKernelGGL(m2m_kernel, dim3(1 << j), dim3(64), 0, st, Ts, Os, (1 << j) - 1, nrhs);
+        launch_xfer<true>(Os, Tt.min_far_level, Ts.J - 1, nrhs, st);
         const int first = (1 << Tt.min_far_level) - 1;
         const int cnt = Tt.ncl - first;
         // radial kernels, d <= 32: node-pair distances on FP64 MFMA
@@ -3625,8 +3712,7 @@ hipError_t launch_eval(const DevTree &Tt, const DevOp &Ot, const DevTree &Ts, co
         case 2: hipLaunchKernelGGL(m2l_cross_kernel<2>, dim3(cnt), dim3(256), 0, st, Tt, Ot, Os, first, nrhs); break;
         default: hipLaunchKernelGGL(m2l_cross_kernel<3>, dim3(cnt), dim3(256), 0, st, Tt, Ot, Os, first, nrhs); break;
         }
-        for (int j = Tt.min_far_level + 1; j <= Tt.J; ++j)
-            hipLaunchKernelGGL(l2l_kernel, dim3(1 << j), dim3(64), 0, st, Tt, Ot, (1 << j) - 1, nrhs);
+        launch_xfer<false>(Ot, Tt.min_far_level + 1, Tt.J, nrhs, st);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     // one rhs, radial kernels, target leaves of at most kSymLeaf points, d <= 32: MFMA nearfield

@@ -99,3 +99,32 @@ def test_eval(orc, case):
     e = rel(yd.cpu().numpy(), orc.Eval(P, T).apply(x))
     say(f"   relative error vs oracle {e:.2e}")
     assert e <= TOL
+
+
+@pytest.mark.parametrize("n,d,q,leaf,nrhs", [(33000, 6, 4, 4, 2), (33000, 6, 4, 4, 17), (9000, 6, 8, 8, 16), (5000, 3, 6, 2, 32)])
+def test_several_rhs_transfers(n, d, q, leaf, nrhs):
+    """Moments and locals of every cluster: each column of a several-rhs pass (MFMA, levels joined in
+    groups) against the one-rhs pass of that column.  Both sum the same products in FP64: within
+    n_x J eps of the largest value, 128 * 14 * 1.1e-16 = 2e-13, taken per array."""
+    X, b = W.points(n, d, 2.0, 80 + n), W.dim_weights(d, 2.0)
+    x = np.random.default_rng(81 + n).standard_normal((n, nrhs))
+    tree = dw.build_tree(torch.from_numpy(X).cuda(), b, leaf, 0.8)
+    op = dw.fmm_create(tree, "matern32", 1.0, q, max_nrhs=nrhs)
+    say(f"[pieces] transfers n={n} J={tree.J} n_x={op.nx} nrhs={nrhs}")
+    xd = torch.from_numpy(x).cuda()
+    yd = torch.empty_like(xd)
+    dw.fmm_matvec(op, xd, yd, parts=2)
+    m, l = op.moments(nrhs)
+    for r in {0, nrhs // 2, nrhs - 1}:
+        x1 = xd[:, r:r + 1].contiguous()
+        y1 = torch.empty_like(x1)
+        dw.fmm_matvec(op, x1, y1, parts=2)
+        m1, l1 = op.moments(1)
+        lv = slice((1 << min_far_level(tree)) - 1, None)
+        assert np.abs(m[lv, :, r] - m1[lv, :, 0]).max() <= 2e-13 * np.abs(m1).max()
+        assert np.abs(l[lv, :, r] - l1[lv, :, 0]).max() <= 2e-13 * np.abs(l1).max()
+
+
+def min_far_level(tree):
+    c = int(np.flatnonzero(np.diff(tree.host()["Fptr"]))[0])
+    return (c + 1).bit_length() - 1
