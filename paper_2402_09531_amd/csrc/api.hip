@@ -651,6 +651,8 @@ extern "C" dwfmm_status dwfmm_fmm_create(dwfmm_tree tree, dwfmm_kernel kernel, d
     }
     D.matern_in_range = kernel.kind == DWFMM_MATERN32 &&
                         std::sqrt(tree->near_reach2) * (1.7320508075688772 * 1.4426950408889634) / kernel.ell <= 1000.0;
+    D.exp_in_range = kernel.kind == DWFMM_EXPONENTIAL &&
+                     std::sqrt(tree->near_reach2) * 1.4426950408889634 / kernel.ell <= 1000.0;
     D.nx = nx;
     D.max_nrhs = o.max_nrhs;
     D.nodes = dnodes;
@@ -1393,13 +1395,16 @@ static dwfmm_status batch_build(const dwfmm_op *ops, int32_t count, int32_t flag
     }
     auto key = [&](const BatchItem &I, bool far_list) {
         // the FP64 nearfield of a split Gaussian runs its own kernel variant (kind 4), the FP64
-        // nearfield of a Matern kernel within the exponent range its unclamped variant (kind 5)
+        // nearfield of a Matern or exponential kernel within the exponent range its unclamped variant
+        // (kinds 5 and 6)
         const int kind = !far_list && I.O.kind == DWFMM_GAUSSIAN &&
                                  (I.precision == 0 ? I.O.gauss_split : I.O.gauss_split32)
                              ? 4
                              : (!far_list && I.O.kind == DWFMM_MATERN32 && I.precision == 0 && I.O.matern_in_range
                                     ? 5
-                                    : I.O.kind);
+                                    : !far_list && I.O.kind == DWFMM_EXPONENTIAL && I.precision == 0 && I.O.exp_in_range
+                                          ? 6
+                                          : I.O.kind);
         return std::vector<int>{kind, (I.T.d + 3) / 4 * 4, far_list ? I.O.nxp / 16 : 0, I.precision != 0};
     };
     std::vector<std::vector<int>> keys;
@@ -2633,6 +2638,9 @@ extern "C" dwfmm_status dwfmm_eval_create(dwfmm_op op, const double *targets, in
             }
         }
         O.gauss_split = O.kind == DWFMM_GAUSSIAN && bmax2 / O.ell <= 300.0;
+        O.matern_in_range = O.kind == DWFMM_MATERN32 &&
+                            std::sqrt(bmax2) * (1.7320508075688772 * 1.4426950408889634) / O.ell <= 1000.0;
+        O.exp_in_range = O.kind == DWFMM_EXPONENTIAL && std::sqrt(bmax2) * 1.4426950408889634 / O.ell <= 1000.0;
     }
     if ((e = hipMemsetAsync(dL, 0, sizeof(double) * H.ncl * nx * R, st)) != hipSuccess ||
         (e = launch_basis(D, nx, dclo, dcsc, dcoff, op->b_lidx, op->b_nnz, op->b_Vinv, op->b_nleg, op->b_la, op->b_ld,

@@ -76,6 +76,68 @@ __device__ __forceinline__ double exp2_bounded(double t)
 // 2^t for t <= 0: arguments below -1075 (where 2^t underflows to zero) are clamped.
 __device__ __forceinline__ double exp2_nonpos(double t) { return exp2_bounded(fmax(t, -1075.0)); }
 
+// 2^(j / 1024), j = 0 ... 1023, correctly rounded, with j << 10 taken off the high word: adding
+// n << 10 to it (n = 1024 e + j) then leaves e in the exponent.  Built by the compiler: powers of
+// 2^(1/1024) in 126-bit fixed point.
+struct Exp2Table {
+    uint64_t v[1024];
+};
+constexpr Exp2Table make_exp2_table()
+{
+    Exp2Table t{};
+    const uint64_t s1 = 0x400b18178ba33b14, s0 = 0x1b486ff22688e804;  // 2^(1/1024) 2^126
+    unsigned __int128 x = (unsigned __int128)1 << 126;
+    for (uint64_t j = 0; j < 1024; ++j) {
+        const uint64_t m = (uint64_t)((x + ((unsigned __int128)1 << 73)) >> 74);  // 53 bits, leading one included
+        t.v[j] = ((uint64_t)1022 << 52) + m - (j << 42);
+        const uint64_t x1 = (uint64_t)(x >> 64), x0 = (uint64_t)x;
+        const unsigned __int128 mid = (unsigned __int128)x1 * s0 + (unsigned __int128)x0 * s1 +
+                                      (((unsigned __int128)x0 * s0) >> 64);
+        x = (((unsigned __int128)x1 * s1) << 2) + (mid >> 62);
+    }
+    return t;
+}
+__device__ constexpr Exp2Table kExp2Table = make_exp2_table();
+constexpr int kExp2Size = 1024;
+
+// The table into LDS, by the whole workgroup; a barrier has to follow.
+__device__ __forceinline__ void load_exp2_table(uint2 *tab)
+{
+    for (int i = threadIdx.x; i < kExp2Size; i += blockDim.x) tab[i] = reinterpret_cast<const uint2 *>(kExp2Table.v)[i];
+}
+
+// 2^f - 1 for |f| <= 2^-11 as a cubic without constant term (csrc/gen_exp_coeffs.py; error 9.4e-17).
+__device__ __forceinline__ double exp2m1_short(double f)
+{
+    double p = 0.05550410866482158;
+    p = fma(p, f, 0.24022650885880065);
+    p = fma(p, f, 0.6931471805599453);
+    return p * f;
+}
+
+// 2^(n / 1024 + f), n in the low word of m = n / 1024 + 1.5 2^42.
+__device__ __forceinline__ double exp2_tab_split(double m, double f, const uint2 *tab)
+{
+    const int n = __double2loint(m);
+    const uint2 w = tab[n & (kExp2Size - 1)];
+    const double v = __hiloint2double((int)(w.y + ((uint32_t)n << 10)), (int)w.x);
+    return fma(v, exp2m1_short(f), v);
+}
+
+// 2^t in FP64 for |t| <= 1020 with the table in LDS: m = t + 1.5 2^42 is t rounded to 1/1024, its
+// low word n = round(1024 t), f = t - n / 1024 exact, 2^t = 2^(n / 1024) (1 + (2^f - 1)).  Seven FP64
+// and three integer operations and one LDS read per value against exp2_bounded's fourteen, and no
+// further off (half an ulp each from the table and the last operation, 9.4e-17 from the cubic).  The
+// FP64 pipe bounds these kernels, so the slots are time: N = 1e6, d = 20 split Gaussian one rhs
+// 11.9 -> 10.95 ms per matvec; N = 3e5, d = 20 exponential 2.64 -> 2.31 ms (with the scaled
+// coordinates below); 2e5 targets and sources, d = 20 Gaussian evaluation 2.25 -> 1.97 ms.
+__device__ __forceinline__ double exp2_tab(double t, const uint2 *tab)
+{
+    constexpr double kRound = 6597069766656.0;  // 1.5 2^42
+    const double m = t + kRound;
+    return exp2_tab_split(m, t - (m - kRound), tab);
+}
+
 // sqrt(x) for x >= 1e-300 (callers clamp; below that the kernels are 1 to double precision):
 // with y the hardware reciprocal square root and g = x y, e = 1 - g y is small (about twice
 // the seed's relative error) and sqrt(x) = g (1 - e)^(-1/2) = g (1 + e/2 + 3e^2/8 + ...).
@@ -133,6 +195,26 @@ __device__ __forceinline__ double matern_s2(double s2)
         const double e = ldexp(exp2_frac(fma(s, -kLog2e, -n)), __double2loint(m));
         return fma(s, e, e);
     }
+}
+
+// matern_s2<false> with 2^(-s log2(e)) from the table: the product is formed exactly inside both of
+// its uses.
+__device__ __forceinline__ double matern_s2_tab(double s2, const uint2 *tab)
+{
+    constexpr double kLog2e = 1.4426950408889634, kRound = 6597069766656.0;
+    const double s = sqrt_pos(fabs(s2) + 1e-300);
+    const double m = fma(s, -kLog2e, kRound);
+    const double e = exp2_tab_split(m, fma(s, -kLog2e, -(m - kRound)), tab);
+    return fma(s, e, e);
+}
+
+// e^(-r / ell) from s^2 = (r log2(e) / ell)^2, for callers whose coordinates are already scaled by
+// log2(e) / ell and that guarantee s <= 1000: the guard of matern_s2, then 2^-s (from the table if TAB).
+template <bool TAB>
+__device__ __forceinline__ double exponential_s2(double s2, const uint2 *tab)
+{
+    const double t = -sqrt_pos(fabs(s2) + 1e-300);
+    return TAB ? exp2_tab(t, tab) : exp2_bounded(t);
 }
 
 template <int KIND>
@@ -788,6 +870,14 @@ constexpr int kGaussSplit = 4;
 // nearfield distances keep every exponent s log2(e) within 1000 (matern_in_range), evaluated
 // without the underflow clamp.
 constexpr int kMaternInRange = 5;
+// The same for the exponential kernel (exp_in_range): no clamp, coordinates scaled by log2(e) / ell and
+// 2^-s from the table in LDS.  It and the split Gaussian use the table; the clamped kernels keep the
+// polynomial (the table with a clamp and subnormal results was 2.5% slower at d = 7), and so does
+// Matern: CG amplifies the last bit of a matvec (1e-15) to 1e-8 in a solution that stopped at 1e-8,
+// and the solves of that kernel were to keep their results.
+constexpr int kExpInRange = 6;
+template <int KIND>
+constexpr bool uses_tab() { return KIND == kGaussSplit || KIND == kExpInRange; }
 template <int KIND>
 constexpr bool is_matern() { return KIND == 0 || KIND == kMaternInRange; }
 constexpr int kSymSeg = 256;  // owned blocks per column-stream segment (= threads per workgroup)
@@ -804,7 +894,7 @@ template <int KIND, int NKC, bool DIAG, bool NK>
 __device__ __forceinline__ void sym_block(const double (&A)[2][NKC], const double (&rN)[2][4],
                                           const double (&rQ)[2][4], double (&racc)[2][4], const double *sX,
                                           const double *sN, const double *sQ, double *colpart, int ns, int ntiles,
-                                          int w, int li, int lg, double inv_ell)
+                                          int w, int li, int lg, double inv_ell, const uint2 *tab)
 {
     const int rt[2] = {w, w + 4};
     const int nct = (ns + 15) / 16;
@@ -834,15 +924,18 @@ __device__ __forceinline__ void sym_block(const double (&A)[2][NKC], const doubl
             for (int v = 0; v < 4; ++v) {
                 double kv;
                 if constexpr (KIND == kGaussSplit) {
-                    kv = exp2_bounded(G[v]);  // the row operand carries log2(e)
+                    kv = exp2_tab(G[v], tab);  // the row operand carries log2(e)
                 } else {
                     double r2 = NK ? G[v] : G[v] + nb;
                     if constexpr (DIAG) {
                         if (16 * rt[u] + 4 * v + lg == j) r2 = 0.0;
                     }
                     // Matern: the coordinates carry sqrt(3) / ell, so r2 is s^2
+                    // (exponential in range: log2(e) / ell)
                     if constexpr (is_matern<KIND>())
                         kv = matern_s2<KIND == 0>(r2);
+                    else if constexpr (KIND == kExpInRange)
+                        kv = exponential_s2<true>(r2, tab);
                     else
                         kv = kernel_fast<KIND>(r2, inv_ell);
                 }
@@ -865,12 +958,16 @@ __device__ __forceinline__ void p2p_sym_body(const DevTree &T, const DevOp &O, i
     __shared__ double sX[DK * kSymLeaf];  // [k][j] shifted source coordinates
     // sN, colF and colJ alternate between two halves from chunk to chunk (nb): the column sums of one
     // chunk read them while the next chunk's staging writes the other half
-    __shared__ double sN[2 * kSymLeaf], sQ[kSymLeaf], tN[kSymLeaf], tQ[kSymLeaf];
+    // (40360 bytes at DK = 20: four workgroups per CU)
+    __shared__ double sN[2 * kSymLeaf], sQ[kSymLeaf], tN[kSymLeaf];
     __shared__ double colpart[4 * kSymLeaf];
+    double *const tQ = colpart;                           // row charges, read before the first column sums
+    __shared__ uint2 tab[uses_tab<KIND>() ? kExp2Size : 1];
     __shared__ double cen[DK];
-    __shared__ int32_t sPre[kSymSeg + 1], sBlk[kSymSeg];  // owned-block segment: size prefix, block ids
+    __shared__ int32_t sPre[kSymSeg + 1];                 // owned-block segment: size prefix
     __shared__ int32_t sBeg[kSymSeg];                     // first source point of each block
-    __shared__ int32_t colF[2 * kSymLeaf], colJ[2 * kSymLeaf];  // block and point of each stream column
+    __shared__ int32_t colF[2 * kSymLeaf];                // block of each stream column
+    __shared__ uint8_t colJ[2 * kSymLeaf];                // its point in the block
     __shared__ int32_t sDiag;                             // the leaf owns its self block
 
     const int c = T.leaf_first + l;
@@ -882,12 +979,14 @@ __device__ __forceinline__ void p2p_sym_body(const DevTree &T, const DevOp &O, i
     const double inv_ell = 1.0 / O.ell;
     const int ntiles = (nt + 15) / 16;
     // Matern: shifted coordinates are scaled by sqrt(3) / ell, so the Gram tile gives s^2 = 3 r^2 / ell^2
-    constexpr bool kMat = is_matern<KIND>();
-    const double csc = kMat ? 1.7320508075688772 * inv_ell : 1.0;
+    // (the exponential in range: log2(e) / ell, s = r log2(e) / ell)
+    constexpr bool kMat = is_matern<KIND>() || KIND == kExpInRange;
+    const double csc = is_matern<KIND>() ? 1.7320508075688772 * inv_ell : kMat ? 1.4426950408889634 * inv_ell : 1.0;
 
     if (nt == 0) return;  // an empty leaf owns no block (uniform over the workgroup)
     // Coordinate rows k in [d, DK) are stored as zeros and cen[k] = 0 there, so every load
     // below is unconditional; point indices past the end of a leaf are clamped and masked.
+    if constexpr (uses_tab<KIND>()) load_exp2_table(tab);
     if (tid < DK) cen[tid] = T.center[(size_t)l * DK + tid];
     if (tid == 0) sDiag = 0;
     __syncthreads();
@@ -993,11 +1092,11 @@ __device__ __forceinline__ void p2p_sym_body(const DevTree &T, const DevOp &O, i
         constexpr bool D = decltype(diag)::value;
         if constexpr (KIND != kGaussSplit) {
             if (nk) {
-                sym_block<KIND, NKC, D, true>(A, rN, rQ, racc, sX, sN + nb, sQ, colpart, ns, ntiles, w, li, lg, inv_ell);
+                sym_block<KIND, NKC, D, true>(A, rN, rQ, racc, sX, sN + nb, sQ, colpart, ns, ntiles, w, li, lg, inv_ell, tab);
                 return;
             }
         }
-        sym_block<KIND, NKC, D, false>(A, rN, rQ, racc, sX, sN + nb, sQ, colpart, ns, ntiles, w, li, lg, inv_ell);
+        sym_block<KIND, NKC, D, false>(A, rN, rQ, racc, sX, sN + nb, sQ, colpart, ns, ntiles, w, li, lg, inv_ell, tab);
     };
     // 1) the leaf with itself (sDiag was set before the barrier that precedes rN)
     if (sDiag) {
@@ -1024,7 +1123,6 @@ __device__ __forceinline__ void p2p_sym_body(const DevTree &T, const DevOp &O, i
                 if (sl != l) sz = T.cend[T.leaf_first + sl] - beg;
             }
             sPre[tid + 1] = sz;
-            sBlk[tid] = f;
             sBeg[tid] = beg;
             if (tid == 0) sPre[0] = 0;
         }
@@ -1057,13 +1155,13 @@ __device__ __forceinline__ void p2p_sym_body(const DevTree &T, const DevOp &O, i
                         if (sPre[mid] <= col) lo = mid;
                         else hi = mid - 1;
                     }
-                    fblk = sBlk[lo];
+                    fblk = fb + lo;
                     jl = col - sPre[lo];
                     pidx = sBeg[lo] + jl;  // from LDS: only the coordinates are loaded from memory
                 }
                 stage(j, pidx, ok);
                 colF[nb + j] = fblk;
-                colJ[nb + j] = jl;
+                colJ[nb + j] = (uint8_t)jl;
             }
             __syncthreads();
             block(std::false_type{}, ns);
@@ -1093,10 +1191,10 @@ __device__ __forceinline__ void p2p_sym_body(const DevTree &T, const DevOp &O, i
 
 // Waves per SIMD (also for the batched variant): four for the split Gaussian and the Matern kernel
 // up to d = 20 (128 registers; the few spills sit outside the tile loop; the extra wave beats the
-// third by ~2% for both), three for the exponential kernel up to d = 20 (four were slower there),
-// else what the registers allow.
+// third by ~2% for both) and the exponential in range (N = 3e5, d = 20: 2.38 -> 2.31 ms), three for
+// the clamped exponential up to d = 20 (four were slower there), else what the registers allow.
 template <int KIND, int DK>
-constexpr int sym_waves() { return (KIND == kGaussSplit || is_matern<KIND>()) && DK <= 20 ? 4 : (DK <= 20 || (KIND != kGaussSplit && DK <= 24) ? 3 : 1); }
+constexpr int sym_waves() { return (uses_tab<KIND>() || is_matern<KIND>()) && DK <= 20 ? 4 : (DK <= 20 || (KIND != kGaussSplit && DK <= 24) ? 3 : 1); }
 
 template <int KIND, int DK>
 __global__ __launch_bounds__(256)
@@ -1106,225 +1204,6 @@ void p2p_sym_kernel(DevTree T, DevOp O)
     const int l = T.leaf_order[blockIdx.x];
     if (l < 0) return;  // padding of a shorter XCD segment
     p2p_sym_body<KIND, DK>(T, O, l);
-}
-
-// ---------------------------------------------------------------- MFMA cross nearfield (new points, one rhs)
-// Evaluation at new points: every (target leaf, source leaf) pair of the cross nearfield is its
-// own block (no symmetry to use).  One workgroup per target leaf (at most kSymLeaf points): its
-// rows, shifted to the leaf's first point, stay in registers as in the symmetric kernel; the
-// source leaves of its nearfield list are swept as one stream of points, kSymLeaf columns at a
-// time (sizes prefix-summed in LDS, a binary search per column); the Gram tile r^2 comes from
-// FP64 MFMA, the kernel from kernel_fast.  The row sums get the farfield (L2P) added and are
-// scattered to the caller's order.
-template <int KIND, int NKC>
-__device__ __forceinline__ void cross_block(const double (&A)[2][NKC], const double (&rN)[2][4], double (&racc)[2][4],
-                                            const double *sX, const double *sN, const double *sQ, int ns, int ntiles,
-                                            int w, int li, int lg, double inv_ell)
-{
-    const int rt[2] = {w, w + 4};
-    const int nct = (ns + 15) / 16;
-    for (int ct = 0; ct < nct; ++ct) {
-        const int j = 16 * ct + li;
-        const double nb = KIND == kGaussSplit ? 0.0 : sN[j], qb = sQ[j];
-        double Bf[NKC];
-#pragma unroll
-        for (int kc = 0; kc < NKC; ++kc) Bf[kc] = sX[(4 * kc + lg) * kSymLeaf + j];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            if (rt[u] >= ntiles) continue;  // uniform over the wave
-            // split Gaussian: A carries (2 log2(e) / ell)(x - c), the chain gives the base-2 exponent
-            // of the cross factor, the column factor sits in the charge and the row factor (rN)
-            // is applied to the row sums at the end
-            dbl4 G;
-            if constexpr (KIND == kGaussSplit)
-                G = dbl4{0.0, 0.0, 0.0, 0.0};
-            else
-                G = dbl4{rN[u][0], rN[u][1], rN[u][2], rN[u][3]};
-#pragma unroll
-            for (int kc = 0; kc < NKC; ++kc) G = __builtin_amdgcn_mfma_f64_16x16x4f64(A[u][kc], Bf[kc], G, 0, 0, 0);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const double kv = KIND == kGaussSplit ? exp2_bounded(G[v]) : kernel_fast<KIND>(G[v] + nb, inv_ell);
-                racc[u][v] = fma(kv, qb, racc[u][v]);
-            }
-        }
-    }
-}
-
-template <int KIND, int DK>
-__device__ __forceinline__ void p2p_cross_mfma_body(const DevTree &T, const DevOp &O, const DevTree &Ts,
-                                                    const double *__restrict__ xs, double *__restrict__ y, int do_far,
-                                                    int l)
-{
-    constexpr int NKC = DK / 4;
-    __shared__ double sX[DK * kSymLeaf];
-    __shared__ double sN[kSymLeaf], sQ[kSymLeaf], tN[kSymLeaf];
-    __shared__ double cen[DK];
-    __shared__ int32_t sPre[kSymSeg + 1], sBeg[kSymSeg];
-
-    const int c = T.leaf_first + l;
-    const int cb = T.cbeg[c], nt = T.cend[c] - cb;
-    if (nt == 0) return;  // uniform over the workgroup
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int li = lane & 15, lg = lane >> 4;
-    const int n = T.n, ns_all = Ts.n;
-    const double inv_ell = 1.0 / O.ell;
-    const int ntiles = (nt + 15) / 16;
-    // rows k in [d, DK) of both trees' coordinates are zeros, so the shift is zero there
-    if (tid < DK) cen[tid] = T.Xs[(size_t)tid * n + cb];
-    __syncthreads();
-    if (tid < kSymLeaf) {
-        const bool ok = tid < nt;
-        const int ii = cb + (ok ? tid : nt - 1);
-        double s = 0.0;
-#pragma unroll
-        for (int k = 0; k < DK; ++k) {
-            const double v = T.Xs[(size_t)k * n + ii] - cen[k];
-            s = fma(v, v, s);
-        }
-        if constexpr (KIND == kGaussSplit)
-            tN[tid] = ok ? exp_bounded(-s * inv_ell) : 0.0;  // row factor
-        else
-            tN[tid] = ok ? s : 0.0;
-    }
-    const int rt[2] = {w, w + 4};
-    double A[2][NKC];
-    const double scale = KIND == kGaussSplit ? 2.0 * 1.4426950408889634 * inv_ell : -2.0;
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int i = 16 * rt[u] + li;
-        const bool ok = i < nt;
-        const int ii = cb + (ok ? i : nt - 1);
-#pragma unroll
-        for (int kc = 0; kc < NKC; ++kc) {
-            const int k = 4 * kc + lg;
-            A[u][kc] = ok ? scale * (T.Xs[(size_t)k * n + ii] - cen[k]) : 0.0;
-        }
-    }
-    __syncthreads();
-    double rN[2][4], racc[2][4];
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            rN[u][v] = tN[16 * rt[u] + 4 * v + lg];
-            racc[u][v] = 0.0;
-        }
-    const int f0 = T.Nptr[l], f1 = T.Nptr[l + 1];
-    int chunk = 0;  // the staging threads alternate between waves 0-1 and 2-3 (as in the symmetric kernel)
-    for (int fb = f0; fb < f1; fb += kSymSeg) {
-        const int fe = min(fb + kSymSeg, f1);
-        __syncthreads();  // the previous segment's table is no longer read
-        {
-            int sz = 0, beg = 0;
-            const int f = fb + tid;
-            if (f < fe) {
-                const int sc = Ts.leaf_first + T.Nsrc[f];
-                beg = Ts.cbeg[sc];
-                sz = Ts.cend[sc] - beg;
-            }
-            sPre[tid + 1] = sz;
-            sBeg[tid] = beg;
-            if (tid == 0) sPre[0] = 0;
-        }
-        __syncthreads();
-        for (int off = 1; off < kSymSeg; off <<= 1) {  // inclusive scan of sPre[1..kSymSeg]
-            const int add = tid >= off ? sPre[tid + 1 - off] : 0;
-            __syncthreads();
-            sPre[tid + 1] += add;
-            __syncthreads();
-        }
-        const int total = sPre[kSymSeg];
-        for (int c0 = 0; c0 < total; c0 += kSymLeaf, ++chunk) {
-            const int ns = min(kSymLeaf, total - c0);
-            const int sid = tid ^ ((chunk & 1) << 7);
-            __syncthreads();  // the previous chunk's tiles are consumed
-            if (sid < kSymLeaf) {
-                const int j = sid;
-                const bool ok = j < ns;
-                int pidx = 0;  // any valid source point for the padding columns
-                if (ok) {
-                    // the list entry holding stream column c0 + j: the largest k with sPre[k] <= c0 + j
-                    const int col = c0 + j;
-                    int lo = 0, hi = kSymSeg;
-                    while (lo < hi) {
-                        const int mid = (lo + hi + 1) >> 1;
-                        if (sPre[mid] <= col) lo = mid;
-                        else hi = mid - 1;
-                    }
-                    pidx = sBeg[lo] + (col - sPre[lo]);
-                }
-                double xv[DK];
-#pragma unroll
-                for (int k = 0; k < DK; ++k) xv[k] = Ts.Xs[(size_t)k * ns_all + pidx];
-                double s = 0.0;
-#pragma unroll
-                for (int k = 0; k < DK; ++k) {
-                    const double v = ok ? xv[k] - cen[k] : 0.0;
-                    sX[k * kSymLeaf + j] = v;
-                    s = fma(v, v, s);
-                }
-                sN[j] = s;
-                if constexpr (KIND == kGaussSplit)
-                    sQ[j] = ok ? xs[pidx] * exp_bounded(-s * inv_ell) : 0.0;  // charge times column factor
-                else
-                    sQ[j] = ok ? xs[pidx] : 0.0;
-            }
-            __syncthreads();
-            cross_block<KIND, NKC>(A, rN, racc, sX, sN, sQ, ns, ntiles, w, li, lg, inv_ell);
-        }
-    }
-    // row sums: reduce over the 16 column lanes, then farfield (L2P) and the scatter
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            double s = racc[u][v];
-            s += __shfl_xor(s, 1, 64);
-            s += __shfl_xor(s, 2, 64);
-            s += __shfl_xor(s, 4, 64);
-            s += __shfl_xor(s, 8, 64);
-            if constexpr (KIND == kGaussSplit) s *= rN[u][v];  // row factor
-            const int i = 16 * rt[u] + 4 * v + lg;
-            if (li == 0) tN[i] = s;
-        }
-    __syncthreads();
-    if (tid < nt) {
-        double acc = tN[tid];
-        if (do_far) {
-            const double *lc = O.L + (size_t)c * O.nx;
-            for (int a = 0; a < O.nx; ++a) acc = fma(O.Lb[(size_t)a * n + cb + tid], lc[a], acc);
-        }
-        y[T.perm[cb + tid]] = acc;
-    }
-}
-
-template <int KIND, int DK>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KIND == kGaussSplit && DK <= 20 ? 4 : (DK <= 24 ? 3 : 1), 8)))
-void p2p_cross_mfma_kernel(DevTree T, DevOp O, DevTree Ts, const double *__restrict__ xs, double *__restrict__ y,
-                           int do_far)
-{
-    const int l = T.near_order[blockIdx.x];
-    if (l < 0) return;  // padding of a shorter XCD segment
-    p2p_cross_mfma_body<KIND, DK>(T, O, Ts, xs, y, do_far, l);
-}
-
-template <int KIND>
-hipError_t launch_cross_mfma_k(const DevTree &Tt, const DevOp &Ot, const DevTree &Ts, const double *xs, double *y,
-                               int do_far, hipStream_t st)
-{
-    switch (Tt.dpad) {
-#define DWFMM_XM(D)                                                                                        \
-    case D:                                                                                                \
-        hipLaunchKernelGGL((p2p_cross_mfma_kernel<KIND, D>), dim3(Tt.n_near_order), dim3(256), 0, st, Tt, Ot, Ts, xs, y, \
-                           do_far);                                                                        \
-        break;
-        DWFMM_XM(4) DWFMM_XM(8) DWFMM_XM(12) DWFMM_XM(16) DWFMM_XM(20) DWFMM_XM(24) DWFMM_XM(28) DWFMM_XM(32)
-#undef DWFMM_XM
-    default:
-        return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- MFMA nearfield, several rhs
@@ -1347,19 +1226,34 @@ constexpr int q_stride() { return RB == 0 ? 1 : 16 * RB; }
 template <int RB>
 __device__ __forceinline__ int q_col(int j, int r) { return RB == 2 ? r ^ ((j & 1) << 4) : r; }
 constexpr int kSX64 = kSymLeaf + 16;
+// LDS of the kernel below without the exp2 table, and whether the table (8 KB) is used: by the
+// kernels in range and the split Gaussian where it leaves as many workgroups per CU (160 KB) as the
+// kernel has without it, at most the four that its registers allow.  (The square operator's Matern
+// runs the clamped kernel here: see kExpInRange.)
+constexpr int mrhs_lds(int dk, int rb) { return 8 * (dk * (kSX64 + 1) + kSymLeaf * (rb == 0 ? 3 : 16 * rb + 2)) + 4 * (2 * kSymSeg + kSymLeaf + 8); }
+constexpr int mrhs_wgs(int lds) { return 163840 / lds < 4 ? 163840 / lds : 4; }
+// The split Gaussian of the square operator keeps the polynomial, since its matvec closes the
+// refinement solves of the reduced precisions (a last bit there moved their alpha by 5e-9).
+template <int KIND, int DK, int RB, bool CROSS>
+constexpr bool mrhs_tab()
+{
+    return (KIND == kExpInRange || (KIND == kGaussSplit && CROSS) || KIND == kMaternInRange) &&
+           mrhs_wgs(mrhs_lds(DK, RB) + 8 * kExp2Size) == mrhs_wgs(mrhs_lds(DK, RB));
+}
 
-// The squared distance of target i (of tree T, shifted by cen) and staged source column j from the
-// coordinate differences themselves.  With the Gram form the rounding of |x|^2 + |y|^2 - 2 x.y is
+// The squared distance of target i (of tree T, shifted by cen and scaled by csc) and staged source
+// column j from the coordinate differences themselves.  With the Gram form the rounding of |x|^2 + |y|^2 - 2 x.y is
 // that of the norms, which the exponential kernel's sqrt turns into an error of the kernel value
 // for nearly coincident points; the caller takes this form there (1e-4 of the norms and below: rare
 // in more than two dimensions, and the error it leaves elsewhere is 5e-14 of the points' distance
 // from the shift over ell).
 template <int DK>
-__device__ __forceinline__ double r2_direct(const DevTree &T, const double *cen, int i, const double *sX, int j)
+__device__ __forceinline__ double r2_direct(const DevTree &T, const double *cen, double csc, int i, const double *sX, int j)
 {
     double r2 = 0.0;
+#pragma unroll 1  // (unrolled, its loads cost the tile loop a wave per SIMD)
     for (int k = 0; k < DK; ++k) {
-        const double t = (T.Xs[(size_t)k * T.n + i] - cen[k]) - sX[k * kSX64 + j];
+        const double t = csc * (T.Xs[(size_t)k * T.n + i] - cen[k]) - sX[k * kSX64 + j];
         r2 = fma(t, t, r2);
     }
     return r2;
@@ -1370,9 +1264,11 @@ template <int KIND, int DK, int RB, bool DIAG, bool CROSS>
 __device__ __forceinline__ void mrhs_block(const double (&Bt)[2][DK / 4], const double (&tn)[2], dbl4 (&Y)[2][RB == 0 ? 1 : RB],
                                            double (&racc)[2], const double *sX, const double *sN, const double *sQ,
                                            int ns, int ntiles, int w, int li, int lg, double inv_ell,
-                                           const DevTree &T, const double *cen, const int (&near_i)[2])
+                                           const DevTree &T, const double *cen, const int (&near_i)[2],
+                                           const uint2 *tab)
 {
     constexpr int NKC = DK / 4;
+    constexpr bool kTab = mrhs_tab<KIND, DK, RB, CROSS>();
     const int rt[2] = {w, w + 4};
     const int nct = (ns + 15) / 16;
     for (int ct = 0; ct < nct; ++ct) {
@@ -1409,16 +1305,25 @@ __device__ __forceinline__ void mrhs_block(const double (&Bt)[2][DK / 4], const 
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 if constexpr (KIND == kGaussSplit) {
-                    Kv[v] = exp2_bounded(G[v]);
+                    Kv[v] = kTab ? exp2_tab(G[v], tab) : exp2_bounded(G[v]);
                 } else {
-                    double r2 = fmax(fma(-2.0, G[v], tn[u] + snv[v]), 0.0);
+                    // (the kernels in range: the coordinates carry their scale, so r2 is s^2)
+                    double r2 = fma(-2.0, G[v], tn[u] + snv[v]);
+                    if constexpr (KIND != kExpInRange && KIND != kMaternInRange) r2 = fmax(r2, 0.0);
                     if constexpr (DIAG) {
                         if (16 * rt[u] + li == 16 * ct + 4 * v + lg) r2 = 0.0;
                     }
-                    if constexpr (CROSS && KIND == 2) {
-                        if (r2 <= 1e-4 * (tn[u] + snv[v])) r2 = r2_direct<DK>(T, cen, near_i[u], sX, 16 * ct + 4 * v + lg);
+                    if constexpr (CROSS && (KIND == 2 || KIND == kExpInRange)) {
+                        if (r2 <= 1e-4 * (tn[u] + snv[v]))
+                            r2 = r2_direct<DK>(T, cen, KIND == kExpInRange ? 1.4426950408889634 * inv_ell : 1.0, near_i[u], sX,
+                                               16 * ct + 4 * v + lg);
                     }
-                    Kv[v] = kernel_fast<KIND>(r2, inv_ell);
+                    if constexpr (KIND == kExpInRange)
+                        Kv[v] = exponential_s2<kTab>(r2, tab);
+                    else if constexpr (KIND == kMaternInRange)
+                        Kv[v] = kTab ? matern_s2_tab(r2, tab) : matern_s2<false>(r2);
+                    else
+                        Kv[v] = kernel_fast<KIND>(r2, inv_ell);
                 }
             }
             if constexpr (RB == 0) {
@@ -1470,6 +1375,8 @@ __device__ __forceinline__ void p2p_mrhs_body(const DevTree &T, const DevOp &O, 
     const int n = T.n, ns_all = CROSS ? Ts.n : n;
     const double inv_ell = 1.0 / O.ell;
     const int ntiles = (nt + 15) / 16;
+    __shared__ uint2 tab[mrhs_tab<KIND, DK, RB, CROSS>() ? kExp2Size : 1];
+    if constexpr (mrhs_tab<KIND, DK, RB, CROSS>()) load_exp2_table(tab);
     // the shift: the leaf's box midpoint, or (target trees of evaluation plans) the first target
     if (tid < DK) cen[tid] = !CROSS || T.center ? T.center[(size_t)l * DK + tid] : T.Xs[(size_t)tid * n + cb];
     __syncthreads();
@@ -1478,6 +1385,8 @@ __device__ __forceinline__ void p2p_mrhs_body(const DevTree &T, const DevOp &O, 
     double Bt[2][NKC], tn[2], racc[2] = {0.0, 0.0};
     dbl4 Y[2][RB == 0 ? 1 : RB];
     int near_i[2];
+    const double csc = KIND == kExpInRange ? 1.4426950408889634 * inv_ell : 1.7320508075688772 * inv_ell;
+    auto scaled = [&](double v) { return KIND == kExpInRange || KIND == kMaternInRange ? csc * v : v; };
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         const int i = 16 * rt[u] + li;
@@ -1487,14 +1396,14 @@ __device__ __forceinline__ void p2p_mrhs_body(const DevTree &T, const DevOp &O, 
         double s = 0.0;
 #pragma unroll
         for (int k = 0; k < DK; ++k) {
-            const double v = T.Xs[(size_t)k * n + ii] - cen[k];
+            const double v = scaled(T.Xs[(size_t)k * n + ii] - cen[k]);
             s = fma(v, v, s);
         }
         tn[u] = s;
         constexpr double kCross = 2.0 * 1.4426950408889634;
 #pragma unroll
         for (int kc = 0; kc < NKC; ++kc) {
-            const double v = T.Xs[(size_t)(4 * kc + lg) * n + ii] - cen[4 * kc + lg];
+            const double v = scaled(T.Xs[(size_t)(4 * kc + lg) * n + ii] - cen[4 * kc + lg]);
             Bt[u][kc] = kSplit ? (kCross * inv_ell) * v : v;
         }
 #pragma unroll
@@ -1538,7 +1447,7 @@ __device__ __forceinline__ void p2p_mrhs_body(const DevTree &T, const DevOp &O, 
                 double s = 0.0;
 #pragma unroll
                 for (int k = 0; k < DK; ++k) {
-                    const double v = ok ? xv[k] - cen[k] : 0.0;
+                    const double v = ok ? scaled(xv[k] - cen[k]) : 0.0;
                     sX[k * kSX64 + j] = v;
                     s = fma(v, v, s);
                 }
@@ -1568,7 +1477,7 @@ __device__ __forceinline__ void p2p_mrhs_body(const DevTree &T, const DevOp &O, 
                 __syncthreads();
                 stage_chunk(nt, tid);
                 __syncthreads();
-                mrhs_block<KIND, DK, RB, true, false>(Bt, tn, Y, racc, sX, sN, sQ, nt, ntiles, w, li, lg, inv_ell, T, cen, near_i);
+                mrhs_block<KIND, DK, RB, true, false>(Bt, tn, Y, racc, sX, sN, sQ, nt, ntiles, w, li, lg, inv_ell, T, cen, near_i, tab);
             }
         }
         int chunk = 0;  // the column search and coordinate staging alternate between waves 0-1 and 2-3
@@ -1620,7 +1529,7 @@ __device__ __forceinline__ void p2p_mrhs_body(const DevTree &T, const DevOp &O, 
                 stage_chunk(ns, sid);
                 __syncthreads();
                 mrhs_block<KIND, DK, RB, false, CROSS>(Bt, tn, Y, racc, sX, sN, sQ, ns, ntiles, w, li, lg, inv_ell, T, cen,
-                                                       near_i);
+                                                       near_i, tab);
             }
         }
     }
@@ -3541,7 +3450,7 @@ hipError_t launch_matvec(const DevTree &T, const DevOp &O, const double *x, doub
             switch (O.kind) {
             case 0: e = O.matern_in_range ? launch_sym_k<kMaternInRange>(T, O, st) : launch_sym_k<0>(T, O, st); break;
             case 1: e = O.gauss_split ? launch_sym_k<kGaussSplit>(T, O, st) : launch_sym_k<1>(T, O, st); break;
-            default: e = launch_sym_k<2>(T, O, st); break;
+            default: e = O.exp_in_range ? launch_sym_k<kExpInRange>(T, O, st) : launch_sym_k<2>(T, O, st); break;
             }
             if (e != hipSuccess) return e;
         } else if (near) {  // FP32 (and BF16, whose single-rhs product has nothing to put on the BF16 MFMA)
@@ -3569,7 +3478,10 @@ hipError_t launch_matvec(const DevTree &T, const DevOp &O, const double *x, doub
                 e = O.gauss_split ? launch_mrhs_k<kGaussSplit>(T, O, y, nrhs, near, nfar, st)
                                   : launch_mrhs_k<1>(T, O, y, nrhs, near, nfar, st);
                 break;
-            default: e = launch_mrhs_k<2>(T, O, y, nrhs, near, nfar, st); break;
+            default:
+                e = O.exp_in_range ? launch_mrhs_k<kExpInRange>(T, O, y, nrhs, near, nfar, st)
+                                   : launch_mrhs_k<2>(T, O, y, nrhs, near, nfar, st);
+                break;
             }
         } else {
             e = launch_mrhs_lp(T, O, y, nrhs, near, nfar, precision, st);
@@ -3638,6 +3550,9 @@ hipError_t launch_batch_matvec(const BatchPlan &P, hipStream_t st, const StreamF
         case kMaternInRange:  // FP64 only (the reduced-precision plan keys Matern as kind 0)
             lp ? launch_p2p_batch_k<0, true>(P, L, st) : launch_p2p_batch_k<kMaternInRange, false>(P, L, st);
             break;
+        case kExpInRange:  // FP64 only
+            lp ? launch_p2p_batch_k<2, true>(P, L, st) : launch_p2p_batch_k<kExpInRange, false>(P, L, st);
+            break;
         default: lp ? launch_p2p_batch_k<2, true>(P, L, st) : launch_p2p_batch_k<2, false>(P, L, st); break;
         }
     }
@@ -3668,11 +3583,15 @@ hipError_t launch_pieces(const DevTree &T, const DevOp &O, const DevTree &Ts, co
                          int near, int far, hipStream_t st)
 {
     switch (O.kind) {
-    case 0: return launch_pieces_k<0>(T, O, Ts, xs, y, nrhs, near, far, st);
+    case 0:
+        return O.matern_in_range ? launch_pieces_k<kMaternInRange>(T, O, Ts, xs, y, nrhs, near, far, st)
+                                 : launch_pieces_k<0>(T, O, Ts, xs, y, nrhs, near, far, st);
     case 1:
         return O.gauss_split ? launch_pieces_k<kGaussSplit>(T, O, Ts, xs, y, nrhs, near, far, st)
                              : launch_pieces_k<1>(T, O, Ts, xs, y, nrhs, near, far, st);
-    default: return launch_pieces_k<2>(T, O, Ts, xs, y, nrhs, near, far, st);
+    default:
+        return O.exp_in_range ? launch_pieces_k<kExpInRange>(T, O, Ts, xs, y, nrhs, near, far, st)
+                              : launch_pieces_k<2>(T, O, Ts, xs, y, nrhs, near, far, st);
     }
 }
 
@@ -3715,17 +3634,7 @@ hipError_t launch_eval(const DevTree &Tt, const DevOp &Ot, const DevTree &Ts, co
         launch_xfer<false>(Ot, Tt.min_far_level + 1, Tt.J, nrhs, st);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    // one rhs, radial kernels, target leaves of at most kSymLeaf points, d <= 32: MFMA nearfield
-    if (nrhs == 1 && radial && Tt.max_leaf <= kSymLeaf) {
-        switch (Os.kind) {
-        case 0: return launch_cross_mfma_k<0>(Tt, Ot, Ts, Os.xt, y, far, st);
-        case 1:
-            return Ot.gauss_split ? launch_cross_mfma_k<kGaussSplit>(Tt, Ot, Ts, Os.xt, y, far, st)
-                                  : launch_cross_mfma_k<1>(Tt, Ot, Ts, Os.xt, y, far, st);
-        default: return launch_cross_mfma_k<2>(Tt, Ot, Ts, Os.xt, y, far, st);
-        }
-    }
-    // several rhs or larger leaves (66 KB of LDS at most, as the several-rhs nearfield)
+    // MFMA nearfield (66 KB of LDS at most, as the several-rhs nearfield)
     if (radial && !(Tt.dpad > 28 && nrhs > 16)) return launch_pieces(Tt, Ot, Ts, Os.xt, y, nrhs, 1, far, st);
     switch (Os.kind) {
     case 0: return launch_p2p_cross_k<0>(Tt, Ot, Ts, Os.xt, y, nrhs, far, st);
