@@ -130,7 +130,9 @@ struct dwfmm_op_s {
     int near_filled = 0;  // the BF16 nearfield tile cache holds this operator's tiles
     ~dwfmm_op_s()
     {
-        fork.destroy();
+        if (fork.forked) (void)hipEventDestroy(fork.forked);
+        if (fork.joined) (void)hipEventDestroy(fork.joined);
+        if (fork.side) (void)hipStreamDestroy(fork.side);
         for (auto &t : timers) {
             (void)hipEventDestroy(t.p2p_start);
             (void)hipEventDestroy(t.p2p_stop);
@@ -677,7 +679,9 @@ extern "C" dwfmm_status dwfmm_fmm_create(dwfmm_tree tree, dwfmm_kernel kernel, d
     op->b_Vinv = dVinv;
     op->b_nnz = nnz_max;
     op->b_nleg = (int)leg_axis.size();
-    if ((e = op->fork.create(false)) != hipSuccess) {
+    if ((e = hipStreamCreateWithFlags(&op->fork.side, hipStreamNonBlocking)) != hipSuccess ||
+        (e = hipEventCreateWithFlags(&op->fork.forked, hipEventDisableTiming)) != hipSuccess ||
+        (e = hipEventCreateWithFlags(&op->fork.joined, hipEventDisableTiming)) != hipSuccess) {
         op->arena.release();
         delete op;
         return fail(DWFMM_E_HIP, std::string("operator streams: ") + hipGetErrorString(e));
@@ -1294,7 +1298,11 @@ struct dwfmm_batch_s {
     bool own_fork = false;            // the fork was created for this batch (else a caller's, shared)
     ~dwfmm_batch_s()
     {
-        if (own_fork) fork.destroy();
+        if (own_fork) {
+            if (fork.forked) (void)hipEventDestroy(fork.forked);
+            if (fork.joined) (void)hipEventDestroy(fork.joined);
+            if (fork.side) (void)hipStreamDestroy(fork.side);
+        }
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
     }
@@ -1439,7 +1447,6 @@ static dwfmm_status batch_build(const dwfmm_op *ops, int32_t count, int32_t flag
             for (size_t i = 0; i < lst.size(); ++i) sorted[i] = lst[kv[i].second];
             lst.swap(sorted);
         }
-        double load = 0.0;
         if (!far_list) {
             // Workgroup q runs on XCD q % 8.  The list is cut into 8 contiguous segments of equal
             // nearfield work (consecutive leaves of a problem share source points in the XCD's
@@ -1452,7 +1459,6 @@ static dwfmm_status batch_build(const dwfmm_op *ops, int32_t count, int32_t flag
                 wk[i] = (*item_work[lst[i].x])[lst[i].y];
                 total += wk[i];
             }
-            load = total;
             std::vector<size_t> cut(9, lst.size());
             cut[0] = 0;
             double acc = 0.0;
@@ -1473,11 +1479,9 @@ static dwfmm_status batch_build(const dwfmm_op *ops, int32_t count, int32_t flag
             lst.swap(perm);
         }
         BatchLaunch L{k[0], k[1], k[2], k[3], (int)work.size(), (int)lst.size()};
-        L.load = load;
         work.insert(work.end(), lst.begin(), lst.end());
         (far_list ? P.m2l : P.p2p).push_back(L);
     }
-    std::stable_sort(P.p2p.begin(), P.p2p.end(), [](const BatchLaunch &a, const BatchLaunch &b) { return a.load > b.load; });
     if (work.empty()) work.push_back(make_int2(-1, 0));
     const int nitems = std::max<int>(1, (int)b->items.size());
     BatchItem *d_items;
@@ -1553,28 +1557,26 @@ static dwfmm_status batch_build(const dwfmm_op *ops, int32_t count, int32_t flag
     if (!(flags & DWFMM_BATCH_GRAPH) && !b->items.empty() && shared_fork && shared_fork->side)
         b->fork = *shared_fork;
     else if (!(flags & DWFMM_BATCH_GRAPH) && !b->items.empty() &&
-        (b->own_fork = true, (e = b->fork.create(true)) != hipSuccess)) {
+        (b->own_fork = true,
+         (e = hipStreamCreateWithFlags(&b->fork.side, hipStreamNonBlocking)) != hipSuccess ||
+         (e = hipEventCreateWithFlags(&b->fork.forked, hipEventDisableTiming)) != hipSuccess ||
+         (e = hipEventCreateWithFlags(&b->fork.joined, hipEventDisableTiming)) != hipSuccess)) {
         b->arena.release();
         delete b;
         return fail(DWFMM_E_HIP, std::string("batch streams: ") + hipGetErrorString(e));
     }
     if ((flags & DWFMM_BATCH_GRAPH) && !b->items.empty()) {
-        // capture the batched matvec once, with the branches an eager call has (farfield beside
-        // nearfield, a nearfield branch per kernel variant: in order on one stream the farfield's time
-        // and each variant's last workgroups add up); each call refreshes the x/y pointer arrays,
-        // then replays it
+        // capture the batched matvec once (its stages in order on one stream); each call refreshes
+        // the x/y pointer arrays, then replays it
         hipStream_t cs;
         if ((e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking)) == hipSuccess) {
-            StreamFork cf;
-            e = cf.create(true);
-            if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
+            e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
             if (e == hipSuccess) {
-                hipError_t el = launch_batch_matvec(P, cs, &cf);
+                hipError_t el = launch_batch_matvec(P, cs);
                 e = hipStreamEndCapture(cs, &b->graph);
                 if (el != hipSuccess) e = el;
             }
             if (e == hipSuccess) e = hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0);
-            cf.destroy();
             (void)hipStreamDestroy(cs);
         }
         if (e != hipSuccess) {
@@ -2248,7 +2250,9 @@ dwfmm_server_s::~dwfmm_server_s()
     for (hipStream_t w : worker_streams) (void)hipStreamDestroy(w);
     if (d_cg) (void)hipFree(d_cg);
     if (d_mirror) (void)hipFree(d_mirror);
-    fork.destroy();
+    if (fork.forked) (void)hipEventDestroy(fork.forked);
+    if (fork.joined) (void)hipEventDestroy(fork.joined);
+    if (fork.side) (void)hipStreamDestroy(fork.side);
 }
 
 extern "C" dwfmm_status dwfmm_server_create(size_t budget_bytes, int32_t max_active, int32_t check_every,
@@ -2267,7 +2271,9 @@ extern "C" dwfmm_status dwfmm_server_create(size_t budget_bytes, int32_t max_act
     hipError_t e = hipGetDevice(&s->device);
     if (e == hipSuccess) e = hipMalloc(&s->d_cg, sizeof(CgItem) * max_active);
     if (e == hipSuccess) e = hipMalloc(&s->d_mirror, sizeof(double) * 8 * max_active);
-    if (e == hipSuccess) e = s->fork.create(true);
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&s->fork.side, hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&s->fork.forked, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&s->fork.joined, hipEventDisableTiming);
     for (int w = 0; w < kServerWorkers && e == hipSuccess; ++w) {
         hipStream_t ws = nullptr;
         e = hipStreamCreateWithFlags(&ws, hipStreamNonBlocking);

@@ -90,31 +90,10 @@ struct KernelTimer {
 };
 
 // A second stream and two events with which the farfield (M2M, M2L, L2L) of a one-rhs matvec
-// runs beside the symmetric nearfield: forked after P2M, joined before the combine.  A batch's has
-// two more streams (near) for its nearfield launches, one per kernel variant: on one stream each
-// variant waits for the last workgroups of the one before.
+// runs beside the symmetric nearfield: forked after P2M, joined before the combine.
 struct StreamFork {
-    hipStream_t side = nullptr, near[2] = {nullptr, nullptr};
-    hipEvent_t forked = nullptr, joined = nullptr, near_done[2] = {nullptr, nullptr};
-    hipError_t create(bool batch)
-    {
-        hipError_t e = hipStreamCreateWithFlags(&side, hipStreamNonBlocking);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&forked, hipEventDisableTiming);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&joined, hipEventDisableTiming);
-        for (int k = 0; k < 2 && batch; ++k) {
-            if (e == hipSuccess) e = hipStreamCreateWithFlags(&near[k], hipStreamNonBlocking);
-            if (e == hipSuccess) e = hipEventCreateWithFlags(&near_done[k], hipEventDisableTiming);
-        }
-        return e;
-    }
-    void destroy()
-    {
-        for (hipEvent_t e : {forked, joined, near_done[0], near_done[1]})
-            if (e) (void)hipEventDestroy(e);
-        for (hipStream_t st : {side, near[0], near[1]})
-            if (st) (void)hipStreamDestroy(st);
-        *this = StreamFork();
-    }
+    hipStream_t side = nullptr;
+    hipEvent_t forked = nullptr, joined = nullptr;
 };
 
 // One matvec (or parts of it) on `stream` (with `fork`, partly on its side stream; the result
@@ -199,7 +178,6 @@ struct BatchLaunch {
     int wpc = 4;
     int grid = 0;  // M2L: 0 = one workgroup per 4 / wpc list entries; > 0 = a persistent grid of
                    // this many workgroups striding over the list
-    double load = 0.0;  // P2P: nearfield work of its leaves (largest launch first)
 };
 constexpr int kM2lPersistentGrid = 1024;  // 4 workgroups per CU on 256 CUs
 
@@ -215,8 +193,7 @@ struct BatchPlan {
     std::vector<BatchLaunch> m2l, p2p;
 };
 
-// With `fork`, the farfield stages run on its side stream beside the nearfield and the nearfield
-// launches on up to three streams (same bits).
+// With `fork`, the farfield stages run on its side stream beside the nearfield (same bits).
 hipError_t launch_batch_matvec(const BatchPlan &P, hipStream_t stream, const StreamFork *fork = nullptr);
 // Waves per cluster compiled for an M2L launch with nxt node tiles: 1 only up to two tiles
 // (its per-lane accumulators grow with 4 / wpc x nxt).

@@ -3523,31 +3523,24 @@ hipError_t launch_batch_matvec(const BatchPlan &P, hipStream_t st, const StreamF
     // moments and locals, the nearfield only the row and column sums: with a fork the farfield
     // runs on the side stream beside the nearfield and is joined before the combine
     const bool forked = fork && fork->side && (!P.m2m.empty() || !P.m2l.empty() || !P.l2l.empty());
-    // nearfield launch i runs on stream i mod nq (0: the caller's)
-    const int nq = fork && fork->near[0] ? std::min<int>(3, (int)P.p2p.size()) : 1;
-    hipError_t e = hipSuccess;
     hipStream_t fs = st;
-    if (forked || nq > 1) {
-        e = hipEventRecord(fork->forked, st);
-        if (forked) {
-            if (e == hipSuccess) e = hipStreamWaitEvent(fork->side, fork->forked, 0);
-            fs = fork->side;
-        }
-        for (int k = 0; k < nq - 1 && e == hipSuccess; ++k) e = hipStreamWaitEvent(fork->near[k], fork->forked, 0);
+    if (forked) {
+        hipError_t e = hipEventRecord(fork->forked, st);
+        if (e == hipSuccess) e = hipStreamWaitEvent(fork->side, fork->forked, 0);
         if (e != hipSuccess) return e;
+        fs = fork->side;
     }
     for (auto &lv : P.m2m)
         hipLaunchKernelGGL(m2m_batch_kernel, dim3(lv.second), dim3(256), 0, fs, P.items, P.work + lv.first);
     for (auto &L : P.m2l) (void)launch_batch_m2l(P, L, fs);
     for (auto &lv : P.l2l)
         hipLaunchKernelGGL(l2l_batch_kernel, dim3(lv.second), dim3(256), 0, fs, P.items, P.work + lv.first);
-    if (forked && (e = hipEventRecord(fork->joined, fs)) != hipSuccess) return e;
-    hipStream_t const main_st = st;
-    int turn = 0;
+    if (forked) {
+        hipError_t e = hipEventRecord(fork->joined, fs);
+        if (e != hipSuccess) return e;
+    }
     for (auto &L : P.p2p) {
         const bool lp = L.prec != 0;
-        const int k = turn++ % nq;
-        hipStream_t const st = k == 0 ? main_st : fork->near[k - 1];
         switch (L.kind) {
         case 0: lp ? launch_p2p_batch_k<0, true>(P, L, st) : launch_p2p_batch_k<0, false>(P, L, st); break;
         case 1: lp ? launch_p2p_batch_k<1, true>(P, L, st) : launch_p2p_batch_k<1, false>(P, L, st); break;
@@ -3563,11 +3556,10 @@ hipError_t launch_batch_matvec(const BatchPlan &P, hipStream_t st, const StreamF
         default: lp ? launch_p2p_batch_k<2, true>(P, L, st) : launch_p2p_batch_k<2, false>(P, L, st); break;
         }
     }
-    for (int k = 0; k < nq - 1; ++k)
-        if ((e = hipEventRecord(fork->near_done[k], fork->near[k])) != hipSuccess ||
-            (e = hipStreamWaitEvent(st, fork->near_done[k], 0)) != hipSuccess)
-            return e;
-    if (forked && (e = hipStreamWaitEvent(st, fork->joined, 0)) != hipSuccess) return e;
+    if (forked) {
+        hipError_t e = hipStreamWaitEvent(st, fork->joined, 0);
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(combine_batch_kernel, dim3(P.leaf_cnt), dim3(kSymLeaf), 0, st, P.items, P.ys,
                        P.work + P.leaf_off);
     return hipGetLastError();
