@@ -18,7 +18,9 @@
  *   - Objects are not thread-safe; distinct objects may be used concurrently.
  *   - The library owns all memory of a tree or operator: it is allocated in
  *     dwfmm_build_tree / dwfmm_fmm_create and freed by the destroy calls.
- *     dwfmm_fmm_matvec and dwfmm_fmm_solve allocate nothing.
+ *     dwfmm_fmm_matvec and dwfmm_fmm_solve allocate nothing (but for one page of
+ *     pinned host memory, which the first one-rhs solve of a small problem takes
+ *     for the process).
  */
 #ifndef DWFMM_H
 #define DWFMM_H

@@ -76,6 +76,37 @@ struct Arena {
         }                                                                                         \
     } while (0)
 
+// 64 slots of 64 bytes in one page of pinned host memory, for device-to-host copies that the host
+// does not wait for at once.  One page per process, allocated by the first solve that may use it
+// (about 250 us, too much per operator) and held until the process ends; a slot is taken by an
+// operator's first such solve and given back by its destructor, from any thread.  With all slots
+// taken the caller gets NULL and does without.
+class PinnedSlots {
+    std::mutex m;
+    unsigned char *page = nullptr;
+    uint64_t used = 0;
+
+public:
+    int32_t *take()
+    {
+        std::lock_guard<std::mutex> g(m);
+        if (!page && hipHostMalloc((void **)&page, 4096, hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            page = nullptr;
+        }
+        if (!page || used == ~(uint64_t)0) return nullptr;
+        const int k = __builtin_ctzll(~used);
+        used |= (uint64_t)1 << k;
+        return (int32_t *)(page + 64 * k);
+    }
+    void give(int32_t *p)
+    {
+        std::lock_guard<std::mutex> g(m);
+        used &= ~((uint64_t)1 << (((unsigned char *)p - page) / 64));
+    }
+};
+PinnedSlots g_pinned;
+
 // coordinate rows stored per point: a multiple of 4 (the MFMA k-chunk) up to 32, of 8 beyond
 int pad_dim(int d) { return d <= 32 ? (d + 3) / 4 * 4 : (d + 7) / 8 * 8; }
 
@@ -127,12 +158,20 @@ struct dwfmm_op_s {
     std::vector<KernelTimer> timers;
     size_t timers_used = 0;
     StreamFork fork;  // farfield beside the one-rhs nearfield
+    // Small problems (lookahead): the states of the last two CG iterations in pinned host memory and
+    // the events behind their copies, from the first solve on
+    bool lookahead = false;
+    int32_t *h_state = nullptr;
+    hipEvent_t state_read[2] = {nullptr, nullptr};
     int near_filled = 0;  // the BF16 nearfield tile cache holds this operator's tiles
     ~dwfmm_op_s()
     {
         if (fork.forked) (void)hipEventDestroy(fork.forked);
         if (fork.joined) (void)hipEventDestroy(fork.joined);
         if (fork.side) (void)hipStreamDestroy(fork.side);
+        if (h_state) g_pinned.give(h_state);
+        for (hipEvent_t ev : state_read)
+            if (ev) (void)hipEventDestroy(ev);
         for (auto &t : timers) {
             (void)hipEventDestroy(t.p2p_start);
             (void)hipEventDestroy(t.p2p_stop);
@@ -485,6 +524,16 @@ static std::vector<int64_t> near_tile_offsets(const HostTree &H)
     return off;
 }
 
+// Whether one-rhs CG on this tree reads its state one iteration late (cg_run1): worth it while the
+// matvec it may waste costs less than the ~20 us gaps of the ten or more iterations it saves, so up to
+// about 150 us of nearfield (1.1e-12 s an evaluated entry).
+static bool cg_lookahead(const dwfmm_tree t)
+{
+    double work = 0.0;
+    for (double w : t->leaf_work) work += w;
+    return work <= 1.5e8;
+}
+
 extern "C" dwfmm_status dwfmm_fmm_create(dwfmm_tree tree, dwfmm_kernel kernel, double q, const dwfmm_opts *opts,
                                          void *stream, dwfmm_op *out)
 {
@@ -679,6 +728,7 @@ extern "C" dwfmm_status dwfmm_fmm_create(dwfmm_tree tree, dwfmm_kernel kernel, d
     op->b_Vinv = dVinv;
     op->b_nnz = nnz_max;
     op->b_nleg = (int)leg_axis.size();
+    op->lookahead = cg_lookahead(tree);
     if ((e = hipStreamCreateWithFlags(&op->fork.side, hipStreamNonBlocking)) != hipSuccess ||
         (e = hipEventCreateWithFlags(&op->fork.forked, hipEventDisableTiming)) != hipSuccess ||
         (e = hipEventCreateWithFlags(&op->fork.joined, hipEventDisableTiming)) != hipSuccess) {
@@ -1007,8 +1057,27 @@ hipError_t cg_run1(dwfmm_op op, double lambda, const double *b, double *x, doubl
         return e;
     hstate.assign(3, 0);
     hrr.assign(2, 0.0);
+    // Small problems read the state of iteration k - 1 while iteration k runs: the copy, the wake-up and
+    // the next launches take about 20 us, which a short matvec does not cover, for one matvec too many
+    // at the end (the vector steps of a stopped problem do nothing, so the results are the same).
+    if (op->lookahead && !op->progress && !op->h_state) {
+        for (hipEvent_t &ev : op->state_read)
+            if (!ev && (e = hipEventCreateWithFlags(&ev, hipEventDisableTiming)) != hipSuccess) return e;
+        op->h_state = g_pinned.take();
+    }
+    const bool ahead = op->h_state && !op->progress;
     for (int k = 0; k < max_iter; ++k) {
-        if (k % op->check_every == 0) {
+        if (ahead && k % op->check_every == 0) {
+            const int now = (k / op->check_every) & 1;
+            if ((e = hipMemcpyAsync(op->h_state + now, op->state, sizeof(int32_t), hipMemcpyDeviceToHost, st)) !=
+                    hipSuccess ||
+                (e = hipEventRecord(op->state_read[now], st)) != hipSuccess)
+                return e;
+            if (k >= op->check_every) {
+                if ((e = hipEventSynchronize(op->state_read[now ^ 1])) != hipSuccess) return e;
+                if (op->h_state[now ^ 1] != 0) break;
+            }
+        } else if (k % op->check_every == 0) {
             if ((e = hipMemcpyAsync(hstate.data(), op->state, sizeof(int32_t), hipMemcpyDeviceToHost, st)) !=
                     hipSuccess ||
                 (op->progress &&
@@ -1024,8 +1093,7 @@ hipError_t cg_run1(dwfmm_op op, double lambda, const double *b, double *x, doubl
         }
         if ((e = launch_matvec(T, op->D, op->p, op->q, 1, 3, precision, st, nullptr, &op->fork)) != hipSuccess)
             return e;
-        for (int step : {CG_PQ, CG_ALPHA, CG_XR, CG_BETA, CG_P})
-            if ((e = launch_cg(step, nullptr, 0, 0, it, st)) != hipSuccess) return e;
+        if ((e = launch_cg_iteration(nullptr, 0, 0, it, st)) != hipSuccess) return e;
     }
     if ((e = hipMemcpyAsync(hrr.data(), op->scal, sizeof(double) * 2, hipMemcpyDeviceToHost, st)) != hipSuccess ||
         (e = hipMemcpyAsync(hstate.data(), op->state, sizeof(int32_t) * 3, hipMemcpyDeviceToHost, st)) != hipSuccess)
@@ -1775,7 +1843,7 @@ extern "C" dwfmm_status dwfmm_batch_solve(dwfmm_batch b, double lambda, const do
             }
             dwfmm_status rc = plan.matvec(src, dst, st);
             if (rc != DWFMM_OK) return rc;
-            for (int sstep : {CG_PQ, CG_ALPHA, CG_XR, CG_BETA, CG_P}) HIP_TRY(step(sstep));
+            HIP_TRY(launch_cg_iteration(b->d_cg, P, nblocks, items[0], st));
         }
         HIP_TRY(read_mirror());
         return DWFMM_OK;
@@ -2371,11 +2439,10 @@ extern "C" dwfmm_status dwfmm_server_tick(dwfmm_server s, int32_t *n_active, int
         }
         dwfmm_status rc = dwfmm_batch_matvec(s->batch, s->xs.data(), s->ys.data(), st);
         if (rc != DWFMM_OK) return rc;
-        // the CG update of every active request (FP64, its own scalars on the device): each step
-        // is one launch over all of them
+        // the CG update of every active request (FP64, its own scalars on the device), its launches
+        // over all of them
         const int nact = (int)s->active.size();
-        for (int step : {CG_PQ, CG_ALPHA, CG_XR, CG_BETA, CG_P})
-            HIP_TRY(launch_cg(step, s->d_cg, nact, s->cg_nblocks, s->h_cg[0], st));
+        HIP_TRY(launch_cg_iteration(s->d_cg, nact, s->cg_nblocks, s->h_cg[0], st));
         for (ServerRequest *r : s->active) r->iters++;
         s->ticks++;
         s->t_launch += s->now() - tm;

@@ -3128,25 +3128,31 @@ __global__ __launch_bounds__(256) void dot_final_kernel(const double *__restrict
 // ---------------------------------------------------------------- CG steps for one-rhs problems
 // Sum of u_i v_i over rows [i0, i1) in the order of dot_partial_kernel with one column: thread t
 // takes rows i0 + t + 256 k into two alternating accumulators, then a fixed pairwise tree over the
-// 256 threads.  term(i, u, v) yields the factors of row i and may update vectors first (a row is
-// visited by one thread only).  The sum is valid in thread 0.
-template <class Term>
-__device__ __forceinline__ double block_dot1(int i0, int i1, double *red, Term term)
+// 256 threads.  get(i) reads what row i needs, term(i, row, u, v) yields its factors and may update
+// vectors (a row is visited by one thread only); eight rows are read before the first is used, so
+// that a block of 4096 rows waits for memory twice and not sixteen times.  Valid in thread 0.
+template <class Get, class Term>
+__device__ __forceinline__ double block_dot1(int i0, int i1, double *red, Get get, Term term)
 {
     const int t = threadIdx.x;
-    double s0 = 0.0, s1 = 0.0, u, v;
+    double s[2] = {0.0, 0.0}, u, v;
     int i = i0 + t;
-    for (; i + 256 < i1; i += 512) {
-        term(i, u, v);
-        s0 = fma(u, v, s0);
-        term(i + 256, u, v);
-        s1 = fma(u, v, s1);
+    for (; i + 256 * 7 < i1; i += 256 * 8) {
+        decltype(get(0)) row[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) row[k] = get(i + 256 * k);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            term(i + 256 * k, row[k], u, v);
+            s[k & 1] = fma(u, v, s[k & 1]);
+        }
     }
-    if (i < i1) {
-        term(i, u, v);
-        s0 = fma(u, v, s0);
+    for (int k = 0; i < i1; i += 256, k ^= 1) {
+        term(i, get(i), u, v);
+        if (k) s[1] = fma(u, v, s[1]);
+        else s[0] = fma(u, v, s[0]);
     }
-    red[t] = s0 + s1;
+    red[t] = s[0] + s[1];
     for (int h = 128; h > 0; h >>= 1) {
         __syncthreads();
         if (t < h) red[t] += red[t + h];
@@ -3154,12 +3160,20 @@ __device__ __forceinline__ double block_dot1(int i0, int i1, double *red, Term t
     return red[0];
 }
 
+// rows of the vectors a step reads
+struct Row2 {
+    double a, b;
+};
+struct Row4 {
+    double a, b, c, d;
+};
+
 // The blocks' partial sums of one problem, added as dot_final_kernel adds them (valid in thread 0).
 __device__ __forceinline__ double final_dot1(const double *partial, int nblk, double *red)
 {
     const int t = threadIdx.x;
     double s = 0.0;
-    for (int b = t; b < nblk; b += 256) s += partial[b];
+    for (int b = t; b < nblk; b += 256) s += __hip_atomic_load(&partial[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     red[t] = s;
     for (int h = 128; h > 0; h >>= 1) {
         __syncthreads();
@@ -3174,16 +3188,78 @@ __global__ __launch_bounds__(256) void dot1_partial_kernel(const double *__restr
     __shared__ double red[256];
     const int chunk = (n + gridDim.x - 1) / gridDim.x;
     const int i0 = blockIdx.x * chunk, i1 = min(n, i0 + chunk);
-    const double s = block_dot1(i0, i1, red, [&](int i, double &u, double &v) {
-        u = a[i];
-        v = b[i];
-    });
+    const double s = block_dot1(
+        i0, i1, red, [&](int i) { return Row2{a[i], b[i]}; },
+        [](int, const Row2 &w, double &u, double &v) {
+            u = w.a;
+            v = w.b;
+        });
     if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
 __device__ __forceinline__ bool cg_stepping(const int32_t *state, int max_it)
 {
     return state[0] == 0 && state[1] < max_it;
+}
+
+// The scalar steps of an iteration, by one thread: the step length from p.q, and beta, the count and
+// the convergence check from the new |r|^2.
+__device__ __forceinline__ double cg_alpha(const CgItem &it, double pq)
+{
+    double a = 0.0;
+    it.scal[2] = pq;
+    if (!isfinite(pq) || fabs(pq) <= 1e-300) {
+        it.state[0] = 2;
+    } else {
+        if (pq < 0.0) it.state[2] += 1;
+        a = it.scal[0] / pq;
+    }
+    it.scal[4] = a;
+    return a;
+}
+
+__device__ __forceinline__ double cg_beta(const CgItem &it, double rrn)
+{
+    const double beta = rrn / it.scal[0];
+    it.scal[3] = rrn;
+    it.scal[5] = beta;
+    it.scal[0] = rrn;
+    it.state[1] += 1;
+    if (sqrt(rrn) <= it.rtol * sqrt(it.scal[1])) it.state[0] = 1;
+    return beta;
+}
+
+// p = r + beta p over rows [i0, i1), eight rows of a thread read before the first is written
+__device__ __forceinline__ void cg_direction(int i0, int i1, double beta, double *p, const double *r)
+{
+    int i = i0 + threadIdx.x;
+    for (; i + 256 * 7 < i1; i += 256 * 8) {
+        Row2 w[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) w[k] = Row2{p[i + 256 * k], r[i + 256 * k]};
+#pragma unroll
+        for (int k = 0; k < 8; ++k) p[i + 256 * k] = fma(beta, w[k].a, w[k].b);
+    }
+    for (; i < i1; i += 256) p[i] = fma(beta, p[i], r[i]);
+}
+
+// Block blk of a problem hands in its partial sum (thread 0); true in the workgroup that is the last
+// of the problem's blocks to do so, which then sees all of them.  The count sits behind the partial
+// sums, is zero between launches (CG_START_SUM sets it) and is cleared by the last block.
+__device__ __forceinline__ bool cg_last_block(const CgItem &it, int blk, double s)
+{
+    __shared__ int last;
+    if (threadIdx.x == 0) {
+        uint32_t *count = reinterpret_cast<uint32_t *>(it.partial + kDotBlocks);
+        __hip_atomic_store(&it.partial[blk], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t before = __hip_atomic_fetch_add(count, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        last = before + 1 == (uint32_t)it.nblk;
+        if (last) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (!last) return false;
+    __threadfence();
+    return true;
 }
 
 // Block steps: workgroup g takes block g - blk0 of the problem whose blocks contain g.
@@ -3215,64 +3291,108 @@ __global__ __launch_bounds__(256) void cg_block_kernel(const CgItem *__restrict_
                 x[i] = 0.0;
                 q[i] = 0.0;
             }
-        const double s = block_dot1(i0, i1, red, [&](int i, double &u, double &v) {
-            double qi = q[i];
-            if (lam != 0.0) {
-                qi = fma(lam, x[i], qi);
-                q[i] = qi;
-            }
-            const double ri = b[i] - qi;
-            r[i] = ri;
-            p[i] = ri;
-            u = ri;
-            v = ri;
-        });
+        const double s = block_dot1(
+            i0, i1, red, [&](int i) { return Row4{q[i], x[i], b[i], 0.0}; },
+            [&](int i, const Row4 &w, double &u, double &v) {
+                double qi = w.a;
+                if (lam != 0.0) {
+                    qi = fma(lam, w.b, qi);
+                    q[i] = qi;
+                }
+                const double ri = w.c - qi;
+                r[i] = ri;
+                p[i] = ri;
+                u = ri;
+                v = ri;
+            });
         if (threadIdx.x == 0) it.partial[blk] = s;
         __syncthreads();
-        const double s2 = block_dot1(i0, i1, red, [&](int i, double &u, double &v) {
-            u = b[i];
-            v = b[i];
-        });
+        const double s2 = block_dot1(
+            i0, i1, red, [&](int i) { return b[i]; },
+            [](int, double w, double &u, double &v) {
+                u = w;
+                v = w;
+            });
         if (threadIdx.x == 0) it.partial[kDotBlocks + blk] = s2;
     } else if (STEP == CG_PQ) {
         if (!cg_stepping(it.state, it.max_it)) return;
-        const double s = block_dot1(i0, i1, red, [&](int i, double &u, double &v) {
-            double qi = q[i];
-            if (lam != 0.0) {
-                qi = fma(lam, p[i], qi);
-                q[i] = qi;
-            }
-            u = p[i];
-            v = qi;
-        });
-        if (threadIdx.x == 0) it.partial[blk] = s;
+        const double s = block_dot1(
+            i0, i1, red, [&](int i) { return Row2{q[i], p[i]}; },
+            [&](int i, const Row2 &w, double &u, double &v) {
+                double qi = w.a;
+                if (lam != 0.0) {
+                    qi = fma(lam, w.b, qi);
+                    q[i] = qi;
+                }
+                u = w.b;
+                v = qi;
+            });
+        if (it.nblk > 1) {
+            if (!cg_last_block(it, blk, s)) return;
+            const double pq = final_dot1(it.partial, it.nblk, red);
+            if (threadIdx.x == 0) (void)cg_alpha(it, pq);
+            return;
+        }
+        // One block holds the whole problem: the rest of the iteration here (a thread meets the same
+        // rows in every step)
+        __shared__ double coef;
+        __shared__ int go;
+        if (threadIdx.x == 0) {
+            coef = cg_alpha(it, s);
+            go = it.state[0] == 0;
+        }
+        __syncthreads();
+        if (!go) return;
+        const double a = coef;
+        const double rr = block_dot1(
+            i0, i1, red, [&](int i) { return Row4{x[i], p[i], r[i], q[i]}; },
+            [&](int i, const Row4 &w, double &u, double &v) {
+                x[i] = fma(a, w.b, w.a);
+                const double ri = fma(-a, w.d, w.c);
+                r[i] = ri;
+                u = ri;
+                v = ri;
+            });
+        if (threadIdx.x == 0) {
+            coef = cg_beta(it, rr);
+            go = it.state[0] == 0;
+        }
+        __syncthreads();
+        if (!go) return;
+        cg_direction(i0, i1, coef, p, r);
     } else if (STEP == CG_XR) {
-        if (!cg_stepping(it.state, it.max_it)) return;
+        if (it.nblk == 1 || !cg_stepping(it.state, it.max_it)) return;
         const double a = it.scal[4];
-        const double s = block_dot1(i0, i1, red, [&](int i, double &u, double &v) {
-            x[i] = fma(a, p[i], x[i]);
-            const double ri = fma(-a, q[i], r[i]);
-            r[i] = ri;
-            u = ri;
-            v = ri;
-        });
-        if (threadIdx.x == 0) it.partial[blk] = s;
+        const double s = block_dot1(
+            i0, i1, red, [&](int i) { return Row4{x[i], p[i], r[i], q[i]}; },
+            [&](int i, const Row4 &w, double &u, double &v) {
+                x[i] = fma(a, w.b, w.a);
+                const double ri = fma(-a, w.d, w.c);
+                r[i] = ri;
+                u = ri;
+                v = ri;
+            });
+        if (!cg_last_block(it, blk, s)) return;
+        const double rrn = final_dot1(it.partial, it.nblk, red);
+        if (threadIdx.x == 0) (void)cg_beta(it, rrn);
     } else if (STEP == CG_P) {
-        if (it.state[0] != 0) return;
-        const double beta = it.scal[5];
-        for (int i = i0 + threadIdx.x; i < i1; i += 256) p[i] = fma(beta, p[i], r[i]);
+        // (no direction is needed after the last step)
+        if (it.nblk == 1 || it.state[0] != 0 || it.state[1] >= it.max_it) return;
+        cg_direction(i0, i1, it.scal[5], p, r);
     } else if (STEP == CG_RES) {
         if (it.frozen) return;
         const double *f = it.f, *vv = it.v;
         double *out = it.out;
-        const double s = block_dot1(i0, i1, red, [&](int i, double &u, double &v) {
-            double o = out[i];
-            if (lam != 0.0) o = fma(lam, vv[i], o);
-            o = f[i] - o;
-            out[i] = o;
-            u = o;
-            v = o;
-        });
+        const double s = block_dot1(
+            i0, i1, red, [&](int i) { return Row4{out[i], vv[i], f[i], 0.0}; },
+            [&](int i, const Row4 &w, double &u, double &v) {
+                double o = w.a;
+                if (lam != 0.0) o = fma(lam, w.b, o);
+                o = w.c - o;
+                out[i] = o;
+                u = o;
+                v = o;
+            });
         if (threadIdx.x == 0) it.partial[blk] = s;
     } else if (STEP == CG_ADD) {
         if (it.frozen) return;
@@ -3295,8 +3415,10 @@ __global__ __launch_bounds__(256) void cg_item_kernel(const CgItem *__restrict__
     int32_t *state = it.state;
     const int t = threadIdx.x;
     if (STEP == CG_START_SUM) {
+        uint32_t *count = reinterpret_cast<uint32_t *>(it.partial + kDotBlocks);
         if (it.frozen) {
             if (t == 0) {
+                *count = 0;
                 state[0] = 3;
                 state[1] = 0;
                 state[2] = 0;
@@ -3307,41 +3429,12 @@ __global__ __launch_bounds__(256) void cg_item_kernel(const CgItem *__restrict__
         __syncthreads();
         const double bb = final_dot1(it.partial + kDotBlocks, it.nblk, red);
         if (t == 0) {
+            *count = 0;  // (over a partial sum that bb has taken)
             scal[0] = rr;
             scal[1] = bb;
             state[1] = 0;
             state[2] = 0;
             state[0] = sqrt(rr) <= it.rtol * sqrt(bb) ? 1 : 0;
-        }
-    } else if (STEP == CG_ALPHA) {
-        if (!cg_stepping(state, it.max_it)) {
-            if (t == 0) scal[4] = 0.0;
-            return;
-        }
-        const double pq = final_dot1(it.partial, it.nblk, red);
-        if (t == 0) {
-            scal[2] = pq;
-            double a = 0.0;
-            if (!isfinite(pq) || fabs(pq) <= 1e-300) {
-                state[0] = 2;
-            } else {
-                if (pq < 0.0) state[2] += 1;
-                a = scal[0] / pq;
-            }
-            scal[4] = a;
-        }
-    } else if (STEP == CG_BETA) {
-        if (!cg_stepping(state, it.max_it)) {
-            if (t == 0) scal[5] = 0.0;
-            return;
-        }
-        const double rrn = final_dot1(it.partial, it.nblk, red);
-        if (t == 0) {
-            scal[3] = rrn;
-            scal[5] = rrn / scal[0];
-            scal[0] = rrn;
-            state[1] += 1;
-            if (sqrt(rrn) <= it.rtol * sqrt(scal[1])) state[0] = 1;
         }
     } else if (STEP == CG_RES_SUM) {
         if (it.frozen) return;
@@ -3715,6 +3808,14 @@ hipError_t launch_dot(const double *a, const double *b, int n, int nrhs, double 
     return hipGetLastError();
 }
 
+hipError_t launch_cg_iteration(const CgItem *items, int nitems, int nblocks, const CgItem &one, hipStream_t stream)
+{
+    hipError_t e = launch_cg(CG_PQ, items, nitems, nblocks, one, stream);
+    if (e != hipSuccess || (items ? nblocks == nitems : one.nblk == 1)) return e;
+    if ((e = launch_cg(CG_XR, items, nitems, nblocks, one, stream)) != hipSuccess) return e;
+    return launch_cg(CG_P, items, nitems, nblocks, one, stream);
+}
+
 hipError_t launch_cg(int step, const CgItem *items, int nitems, int nblocks, const CgItem &one, hipStream_t stream)
 {
     if (!items) {
@@ -3732,8 +3833,6 @@ hipError_t launch_cg(int step, const CgItem *items, int nitems, int nblocks, con
     case CG_ADD: hipLaunchKernelGGL(cg_block_kernel<CG_ADD>, blocks, th, 0, stream, items, nitems, one); break;
     case CG_SUB: hipLaunchKernelGGL(cg_block_kernel<CG_SUB>, blocks, th, 0, stream, items, nitems, one); break;
     case CG_START_SUM: hipLaunchKernelGGL(cg_item_kernel<CG_START_SUM>, probs, th, 0, stream, items, one); break;
-    case CG_ALPHA: hipLaunchKernelGGL(cg_item_kernel<CG_ALPHA>, probs, th, 0, stream, items, one); break;
-    case CG_BETA: hipLaunchKernelGGL(cg_item_kernel<CG_BETA>, probs, th, 0, stream, items, one); break;
     case CG_RES_SUM: hipLaunchKernelGGL(cg_item_kernel<CG_RES_SUM>, probs, th, 0, stream, items, one); break;
     case CG_MIRROR: hipLaunchKernelGGL(cg_item_kernel<CG_MIRROR>, probs, th, 0, stream, items, one); break;
     default: return hipErrorInvalidValue;
