@@ -2200,7 +2200,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CM == 2 && 
     __shared__ float sQ[BF16 ? 1 : kSymLeaf * q_stride32<RB>()];
     __shared__ __attribute__((aligned(16))) __bf16 sQt[BF16 ? 16 * RB * kSymLeaf : 8];
     __shared__ double cen[DK];
-    __shared__ int32_t sPre[kSymSeg + 1], sBeg[kSymSeg], colP[kSymLeaf], sDiag;
+    __shared__ int32_t sPre[kSymSeg + 1], sBeg[kSymSeg], colP[2 * kSymLeaf], sDiag;
     constexpr bool kSplit = KIND == kGaussSplit;
     static_assert(CM == 0 || BF16, "the tile cache holds BF16 tiles");
     __shared__ float tF[kSplit ? kSymLeaf : 1];  // split Gaussian: row factors exp(-|x - c|^2 / ell)
@@ -2285,22 +2285,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CM == 2 && 
         for (int f = f0 + tid; f < f1; f += blockDim.x)
             if (T.Nsrc[f] == l) sDiag = 1;
         __syncthreads();
-        // sid: the 128 threads that stage the coordinates (waves 0-1 or 2-3, alternating by chunk)
-        auto stage_chunk = [&](int ns, int sid) {  // columns of colP[0..kSymLeaf), the first ns real
+        // Staging of a chunk's columns colP[cp ... cp + kSymLeaf), the first ns real; padding columns are
+        // any valid point (their kernel values are finite) with zero charges.  sid: the 128 threads that
+        // take the coordinates (waves 0-1 or 2-3, alternating by chunk); the others run ahead().
+        const float col_scale = kSplit ? inv_ell * -1.4426950408889634f : 1.0f;
+        auto stage_chunk = [&](int cp, int ns, int sid, auto ahead) {
             if constexpr (CM != 2) if (sid < kSymLeaf) {  // (the coordinates are not needed to read stored tiles)
                 const int j = sid;
-                const bool ok = j < ns;
-                const int jj = colP[j];
+                const int jj = colP[cp + j];
                 double xv[DK];
 #pragma unroll
                 for (int k = 0; k < DK; ++k) xv[k] = T.Xs[(size_t)k * n + jj];
                 float s = 0.0f;
-#pragma unroll
-                for (int k = 0; k < DK; ++k) {
-                    const float v = ok ? (float)(xv[k] - cen[k]) : 0.0f;
-                    if constexpr (!kH) sX[k * kSX32 + j] = v;
-                    s = fmaf(v, v, s);
-                }
                 if constexpr (kH) {
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
@@ -2308,7 +2304,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CM == 2 && 
 #pragma unroll
                         for (int e = 0; e < 8; ++e) {
                             const int k = 8 * q + e;
-                            const float v = (k < DK && ok) ? (float)(xv[k < DK ? k : 0] - cen[k < DK ? k : 0]) * hs : 0.0f;
+                            const float x = k < DK ? (float)(xv[k < DK ? k : 0] - cen[k < DK ? k : 0]) : 0.0f;
+                            if (k < DK) s = fmaf(x, x, s);
+                            const float v = x * hs;
                             const _Float16 h = (_Float16)v;
                             hv[e] = h;
                             lv[e] = (_Float16)((v - (float)h) * 2048.0f);
@@ -2316,17 +2314,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CM == 2 && 
                         *reinterpret_cast<f16x8 *>(&sXh[gram_slot(0, j >> 4, (j & 15) + 16 * q)]) = hv;
                         *reinterpret_cast<f16x8 *>(&sXh[gram_slot(1, j >> 4, (j & 15) + 16 * q)]) = lv;
                     }
+                } else {
+#pragma unroll
+                    for (int k = 0; k < DK; ++k) {
+                        const float v = (float)(xv[k] - cen[k]);
+                        sX[k * kSX32 + j] = v;
+                        s = fmaf(v, v, s);
+                    }
                 }
                 // split Gaussian: the base-2 logarithm of the column factor exp(-|y - c|^2 / ell)
-                sN[j] = kSplit ? s * (inv_ell * -1.4426950408889634f) : s;
+                sN[j] = kSplit ? s * col_scale : s;
             }
-            // as in the FP64 kernel: every charge load of the thread issued before the first store
+            ahead();
+            // as in the FP64 kernel: every charge load of the thread issued before the first store.
+            // Charges beyond nrhs only enter sums that are not written; those beyond the stream are
+            // zeroed in a chunk that has such columns.
             constexpr int QPT = kSymLeaf * 16 * RB / 256, G = 256 / (16 * RB);
             // FP32: r = tid mod 16 RB.  BF16 (the 8-byte stores in the apply's order): a half-wave
             // takes 16 rhs x 2 neighbouring column groups, 32 consecutive slots
             const int r = BF16 ? (tid & 15) + 16 * ((tid >> 5) % RB) : tid % (16 * RB);
             const int j0 = BF16 ? (((tid >> 5) / RB) << 1) + ((tid >> 4) & 1) : tid / (16 * RB);
             const int rr = r < nrhs ? r : 0;
+            const bool full = ns == kSymLeaf;  // uniform
             if constexpr (BF16) {
                 // charges of the BF16 copy P2M wrote (the values this path rounds the FP64 ones to,
                 // a quarter of their bytes); columns 4 (j0 + G t) + e, e < 4: one 8-byte store of
@@ -2336,23 +2345,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CM == 2 && 
 #pragma unroll
                 for (int t = 0; t < QPT / 4; ++t)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) qb[4 * t + e] = O.xtb[(size_t)colP[4 * (j0 + G * t) + e] * nrhs + rr];
+                    for (int e = 0; e < 4; ++e) qb[4 * t + e] = O.xtb[(size_t)colP[cp + 4 * (j0 + G * t) + e] * nrhs + rr];
+                auto store = [&](auto all) {
 #pragma unroll
-                for (int t = 0; t < QPT / 4; ++t) {
-                    const int j = 4 * (j0 + G * t);
-                    bf16x4 v;
+                    for (int t = 0; t < QPT / 4; ++t) {
+                        const int j = 4 * (j0 + G * t);
+                        bf16x4 v;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = (j + e < ns && r < nrhs) ? qb[4 * t + e] : (__bf16)0.0f;
-                    *reinterpret_cast<bf16x4 *>(&sQt[qt_slot<RB>(j >> 4, r >> 4, (r & 15) + 16 * ((j & 15) >> 2))]) = v;
-                }
+                        for (int e = 0; e < 4; ++e) v[e] = decltype(all)::value || j + e < ns ? qb[4 * t + e] : (__bf16)0.0f;
+                        *reinterpret_cast<bf16x4 *>(&sQt[qt_slot<RB>(j >> 4, r >> 4, (r & 15) + 16 * ((j & 15) >> 2))]) = v;
+                    }
+                };
+                if (full) store(std::true_type{});
+                else store(std::false_type{});
             } else {
                 double qv[QPT];
 #pragma unroll
-                for (int t = 0; t < QPT; ++t) qv[t] = O.xt[(size_t)colP[j0 + t * G] * nrhs + rr];
+                for (int t = 0; t < QPT; ++t) qv[t] = O.xt[(size_t)colP[cp + j0 + t * G] * nrhs + rr];
 #pragma unroll
                 for (int t = 0; t < QPT; ++t) {
                     const int j = j0 + t * G;
-                    sQ[j * q_stride32<RB>() + r] = (j < ns && r < nrhs) ? (float)qv[t] : 0.0f;
+                    sQ[j * q_stride32<RB>() + r] = full || j < ns ? (float)qv[t] : 0.0f;
                 }
             }
         };
@@ -2360,7 +2373,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CM == 2 && 
             if constexpr (CM == 2) load_tiles(pre, ltiles, lcount, nt, ntiles, w, lane);
             if (tid < kSymLeaf) colP[tid] = cb + (tid < nt ? tid : nt - 1);
             __syncthreads();
-            stage_chunk(nt, tid);
+            stage_chunk(0, nt, tid, [] {});
             __syncthreads();
             if constexpr (CM == 2) {
                 apply_tiles<RB>(pre, Y, sQt, nt, ntiles, w, li, lg);
@@ -2394,28 +2407,38 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CM == 2 && 
                 __syncthreads();
             }
             const int total = sPre[kSymSeg];
-            for (int c0 = 0; c0 < total; c0 += kSymLeaf, ++chunk) {
+            // the source point of stream column c0 + j into half h of colP (padding columns: cb)
+            auto search = [&](int c0, int j, int h) {
+                int pidx = cb;
+                const int col = c0 + j;
+                if (col < total) {
+                    int lo = 0, hi = kSymSeg;
+                    while (lo < hi) {
+                        const int mid = (lo + hi + 1) >> 1;
+                        if (sPre[mid] <= col) lo = mid;
+                        else hi = mid - 1;
+                    }
+                    pidx = sBeg[lo] + (col - sPre[lo]);
+                }
+                colP[h * kSymLeaf + j] = pidx;
+            };
+            // The columns of a chunk are found while the chunk before is staged, by the threads that
+            // stage no coordinates, into the other half of colP: only a segment's first search waits.
+            // The kernel is bound by the latency between a chunk's barriers and by VALU work (64 %
+            // busy, a third of it staging, at d = 20 in BF16); with the search off that path and the
+            // selects of padding columns out of the staging, matvecs of 32 rhs: Gaussian, 250k
+            // points, d = 20: FP32 2.64 -> 2.53 ms, BF16 1.144 -> 1.120 ms; Matern-3/2, 200k points,
+            // d = 10, BF16 2.56 -> 2.45 ms.
+            if (tid < kSymLeaf) search(0, tid, 0);
+            int half = 0;
+            for (int c0 = 0; c0 < total; c0 += kSymLeaf, ++chunk, half ^= 1) {
                 const int ns = min(kSymLeaf, total - c0);
                 const int sid = tid ^ ((chunk & 1) << 7);
                 if constexpr (CM == 2) load_tiles(pre, ltiles + tb * 512, lcount - tb, ns, ntiles, w, lane);
-                // no barrier here, as in the FP64 kernel: the search writes only colP, which the previous
-                // chunk's tiles do not read
-                if (sid < kSymLeaf) {
-                    int pidx = cb;
-                    if (sid < ns) {
-                        const int col = c0 + sid;
-                        int lo = 0, hi = kSymSeg;
-                        while (lo < hi) {
-                            const int mid = (lo + hi + 1) >> 1;
-                            if (sPre[mid] <= col) lo = mid;
-                            else hi = mid - 1;
-                        }
-                        pidx = sBeg[lo] + (col - sPre[lo]);
-                    }
-                    colP[sid] = pidx;
-                }
-                __syncthreads();
-                stage_chunk(ns, sid);
+                __syncthreads();  // this chunk's columns are found, the previous tiles are consumed
+                stage_chunk(half * kSymLeaf, ns, sid, [&] {
+                    if (sid >= kSymLeaf && c0 + kSymLeaf < total) search(c0 + kSymLeaf, sid - kSymLeaf, half ^ 1);
+                });
                 __syncthreads();
                 if constexpr (CM == 2) {
                     apply_tiles<RB>(pre, Y, sQt, ns, ntiles, w, li, lg);
