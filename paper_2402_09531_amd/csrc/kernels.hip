@@ -1815,8 +1815,7 @@ __device__ __forceinline__ void p2p_sym32_body(const DevTree &T, const DevOp &O,
     __shared__ float sN[kSymLeaf], sQ[kSymLeaf], tN[kSymLeaf], tQ[kSymLeaf];
     __shared__ float colpart[4 * kSymLeaf];
     __shared__ double cen[DK];
-    __shared__ int32_t sPre[kSymSeg + 1], sBlk[kSymSeg], sBeg[kSymSeg];
-    __shared__ int32_t colF[kSymLeaf], colJ[kSymLeaf];
+    __shared__ int32_t sPre[kSymSeg + 1], sBeg[kSymSeg];
     __shared__ int32_t sDiag;
     const int c = T.leaf_first + l;
     const int cb = T.cbeg[c], nt = T.cend[c] - cb;
@@ -1877,7 +1876,8 @@ __device__ __forceinline__ void p2p_sym32_body(const DevTree &T, const DevOp &O,
             racc[u][v] = 0.0f;
         }
     // Tile column j: point pidx shifted to the owner's midpoint, its squared norm (split
-    // Gaussian: its column factor) and its charge; columns past the data are zero.
+    // Gaussian: its column factor, returned) and its charge; columns past the data are any valid
+    // point with a zero charge.
     auto stage = [&](int j, int pidx, bool ok) {
         double xv[DK];
 #pragma unroll
@@ -1885,18 +1885,19 @@ __device__ __forceinline__ void p2p_sym32_body(const DevTree &T, const DevOp &O,
         float s = 0.0f;
 #pragma unroll
         for (int k = 0; k < DK; ++k) {
-            const float v = ok ? (float)(xv[k] - cen[k]) : 0.0f;
+            const float v = (float)(xv[k] - cen[k]);
             sX[k * kSX32 + j] = v;
             s = fmaf(v, v, s);
         }
         const float q = (float)O.xt[pidx];
         if constexpr (KIND == kGaussSplit) {
             const float bfac = __builtin_amdgcn_exp2f(s * (inv_ell * -1.4426950408889634f));  // column factor
-            sN[j] = bfac;
             sQ[j] = ok ? q * bfac : 0.0f;
+            return bfac;
         } else {
             sN[j] = s;
             sQ[j] = ok ? q : 0.0f;
+            return 1.0f;
         }
     };
     // the leaf with itself when listed, then the other owned blocks as one column stream (as in FP64)
@@ -1919,7 +1920,6 @@ __device__ __forceinline__ void p2p_sym32_body(const DevTree &T, const DevOp &O,
                 if (sl != l) sz = T.cend[T.leaf_first + sl] - beg;
             }
             sPre[tid + 1] = sz;
-            sBlk[tid] = f;
             sBeg[tid] = beg;
             if (tid == 0) sPre[0] = 0;
         }
@@ -1931,38 +1931,44 @@ __device__ __forceinline__ void p2p_sym32_body(const DevTree &T, const DevOp &O,
             __syncthreads();
         }
         const int total = sPre[kSymSeg];
+        // The thread that stages a column also stores its column sum, and is idle in the staging of
+        // the chunk before: it finds its column then and keeps it in registers, so that only a
+        // segment's first search waits and a chunk has two barriers.  (Gaussian, 500k points,
+        // d = 20: 1.95 -> 1.77 ms a matvec; Matern-3/2, d = 10: 300k points 2.62 -> 2.52 ms, one
+        // million 17.5 -> 17.2 ms, where the vector ALU is 80 % busy.  The FP64 kernel is bound by its
+        // pipe and has no registers to spare: there the same change cost 0.5 to 1 %.)
+        int pidx = cb, fblk = 0, jl = 0;
+        auto search = [&](int col) {
+            pidx = cb;
+            if (col < total) {
+                int lo = 0, hi = kSymSeg;
+                while (lo < hi) {
+                    const int mid = (lo + hi + 1) >> 1;
+                    if (sPre[mid] <= col) lo = mid;
+                    else hi = mid - 1;
+                }
+                fblk = fb + lo;
+                jl = col - sPre[lo];
+                pidx = sBeg[lo] + jl;  // from LDS: only the coordinates are loaded from memory
+            }
+        };
+        if ((tid ^ ((chunk & 1) << 7)) < kSymLeaf) search(tid & (kSymLeaf - 1));
         for (int c0 = 0; c0 < total; c0 += kSymLeaf, ++chunk) {
             const int ns = min(kSymLeaf, total - c0);
             const int sid = tid ^ ((chunk & 1) << 7);
-            __syncthreads();
-            if (sid < kSymLeaf) {
-                const int j = sid;
-                const bool ok = j < ns;
-                int pidx = cb, fblk = 0, jl = 0;
-                if (ok) {
-                    const int col = c0 + j;
-                    int lo = 0, hi = kSymSeg;
-                    while (lo < hi) {
-                        const int mid = (lo + hi + 1) >> 1;
-                        if (sPre[mid] <= col) lo = mid;
-                        else hi = mid - 1;
-                    }
-                    fblk = sBlk[lo];
-                    jl = col - sPre[lo];
-                    pidx = sBeg[lo] + jl;  // from LDS: only the coordinates are loaded from memory
-                }
-                stage(j, pidx, ok);
-                colF[j] = fblk;
-                colJ[j] = jl;
-            }
+            // no barrier here: the previous tiles ended at the barrier before their column sums, and
+            // the one after this staging keeps the next tiles' colpart behind those sums
+            float bfac = 1.0f;
+            if (sid < kSymLeaf) bfac = stage(sid, pidx, sid < ns);
+            else search(c0 + sid);
             __syncthreads();
             sym_block32<KIND, NKC, false>(A, rN, rQ, racc, sX, sN, sQ, colpart, ns, ntiles, w, li, lg, inv_ell);
             __syncthreads();
             if (sid < ns) {
                 float cs = ((colpart[sid] + colpart[kSymLeaf + sid]) + colpart[2 * kSymLeaf + sid]) +
                            colpart[3 * kSymLeaf + sid];
-                if constexpr (KIND == kGaussSplit) cs *= sN[sid];
-                O.colbuf[(size_t)colF[sid] * kSymLeaf + colJ[sid]] = (double)cs;
+                if constexpr (KIND == kGaussSplit) cs *= bfac;
+                O.colbuf[(size_t)fblk * kSymLeaf + jl] = (double)cs;
             }
         }
     }
