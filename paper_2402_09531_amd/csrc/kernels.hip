@@ -328,31 +328,63 @@ __global__ __launch_bounds__(256) void p2m_kernel(DevTree T, DevOp O, const doub
     p2m_body(T, O, blockIdx.x, x, nrhs, do_far, xl);
 }
 
-// P2M for several rhs: the leaf's whole block of charges is staged once (rows of nrhs
-// doubles, read and written in order), then every (node, rhs) moment sums over the leaf's
-// points from LDS, in point order.  For leaves of at most 8192 / nrhs points (64 KB of LDS).
+// P2M for several rhs (at most 32): the leaf's whole block of charges is staged once (rows of nrhs
+// doubles, read and written in order; eight rows of a thread are requested before the first is
+// stored), then the moments are products over the leaf's points on FP64 MFMA, which adds them in
+// point order.  For leaves of at most 8192 / nrhs points (64 KB of LDS).  Bound by the gather's
+// bytes: one million points, 32 rhs, n_x = 15 (580 MB) 324 -> 161 us, against a row at a time per
+// thread and a thread per moment.
 __global__ __launch_bounds__(256) void p2m_multi_kernel(DevTree T, DevOp O, const double *__restrict__ x, int nrhs,
                                                         int do_far)
 {
     extern __shared__ double xl[];  // [np][nrhs]
+    constexpr int U = 8;
     const int l = blockIdx.x, c = T.leaf_first + l;
     const int cb = T.cbeg[c], np = T.cend[c] - cb;
-    for (int e = threadIdx.x; e < np * nrhs; e += blockDim.x) {
-        const int i = e / nrhs, r = e - i * nrhs;
-        const double v = x[(size_t)T.perm[cb + i] * nrhs + r];
-        xl[e] = v;
-        O.xt[(size_t)cb * nrhs + e] = v;
-        if (O.xtb) O.xtb[(size_t)cb * nrhs + e] = (__bf16)(float)v;
+    const int per = 256 / nrhs, r = threadIdx.x % nrhs, g = threadIdx.x / nrhs;
+    for (int i0 = g; g < per && i0 < np; i0 += U * per) {
+        int32_t pm[U];
+        double v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) pm[u] = T.perm[cb + min(i0 + u * per, np - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = x[(size_t)pm[u] * nrhs + r];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * per;
+            if (i >= np) break;
+            xl[i * nrhs + r] = v[u];
+            O.xt[(size_t)(cb + i) * nrhs + r] = v[u];
+            if (O.xtb) O.xtb[(size_t)(cb + i) * nrhs + r] = (__bf16)(float)v[u];
+        }
     }
     if (!do_far) return;  // uniform over the workgroup
     __syncthreads();
-    const int nx = O.nx;
-    for (int p = threadIdx.x; p < nx * nrhs; p += blockDim.x) {
-        const int a = p / nrhs, r = p - a * nrhs;
-        const double *lb = O.Lb + (size_t)a * T.n + cb;
-        double s = 0.0;
-        for (int i = 0; i < np; ++i) s = fma(lb[i], xl[i * nrhs + r], s);
-        O.M[((size_t)c * nx + a) * nrhs + r] = s;
+    // a wave per (16 nodes, 16 rhs); padding points are zero in both operands
+    const int nx = O.nx, nxt = (nx + 15) / 16, nrt = (nrhs + 15) / 16;
+    const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
+    for (int p = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); p < nxt * nrt; p += 4) {
+        const int at = p / nrt, rt = p - at * nrt;
+        const double *lb = O.Lb + (size_t)min(16 * at + li, nx - 1) * T.n + cb;
+        const int rr = min(16 * rt + li, nrhs - 1);
+        dbl4 Y = {0.0, 0.0, 0.0, 0.0};
+        for (int i0 = 0; i0 < np; i0 += 4 * U) {
+            double av[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) av[k] = lb[min(i0 + 4 * k + lg, np - 1)];
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                if (i0 + 4 * k >= np) break;  // uniform
+                const int i = i0 + 4 * k + lg;
+                const double bv = xl[min(i, np - 1) * nrhs + rr];
+                Y = __builtin_amdgcn_mfma_f64_16x16x4f64(i < np ? av[k] : 0.0, i < np ? bv : 0.0, Y, 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int a = 16 * at + 4 * v + lg;
+            if (a < nx && 16 * rt + li < nrhs) O.M[((size_t)c * nx + a) * nrhs + 16 * rt + li] = Y[v];
+        }
     }
 }
 
@@ -1692,25 +1724,67 @@ __global__ __launch_bounds__(kSymLeaf) void p2p_combine_kernel(DevTree T, DevOp 
 
 // Farfield evaluation (L2P) added to a several-rhs nearfield result that was computed beside the
 // farfield: y[perm i][r] += sum_a l_a(x_i) L_c[a][r] for the points i of leaf blockIdx.x (the sum
-// over a formed first, in order, then added once).  The leaf's locals sit in LDS (nx * nrhs
-// doubles, dynamic); thread t keeps rhs t mod nrhs and walks the points t / nrhs, t / nrhs + per,
-// ... (per = 256 / nrhs), so the nrhs threads of a point read one basis value and write one row.
+// over a formed first, in order, then added once), as products of (points x nodes) and (nodes x
+// rhs) on FP64 MFMA, which adds the nodes in order: a wave takes 16 points at a time, two such
+// tiles together, RB 16-wide rhs tiles, with the rows of y requested before the products.  Bound by
+// the bytes of y: one million points, 32 rhs, n_x = 15 (630 MB) 357 -> 123 us, against a thread per
+// (point, rhs) with one broadcast basis value per product.
+template <int RB>
 __global__ __launch_bounds__(256) void l2p_add_kernel(DevTree T, DevOp O, double *__restrict__ y, int nrhs)
 {
-    extern __shared__ double sL[];  // [nx][nrhs]
     const int c = T.leaf_first + blockIdx.x;
     const int cb = T.cbeg[c], nt = T.cend[c] - cb;
     const int nx = O.nx;
+    const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
     const double *lc = O.L + (size_t)c * nx * nrhs;
-    for (int e = threadIdx.x; e < nx * nrhs; e += blockDim.x) sL[e] = lc[e];
-    __syncthreads();
-    const int per = blockDim.x / nrhs;
-    const int r = threadIdx.x % nrhs, i0 = threadIdx.x / nrhs;
-    if (i0 >= per) return;  // (no barrier follows)
-    for (int i = i0; i < nt; i += per) {
-        double acc = 0.0;
-        for (int a = 0; a < nx; ++a) acc = fma(O.Lb[(size_t)a * T.n + cb + i], sL[a * nrhs + r], acc);
-        y[(size_t)T.perm[cb + i] * nrhs + r] += acc;
+    int rr[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) rr[rb] = min(16 * rb + li, nrhs - 1);
+    for (int t0 = 16 * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); t0 < nt; t0 += 128) {
+        double *row[2][4];
+        double yv[2][RB][4];
+        dbl4 Y[2][RB];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) row[u][v] = y + (size_t)T.perm[cb + min(t0 + 64 * u + 4 * v + lg, nt - 1)] * nrhs;
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                Y[u][rb] = dbl4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int v = 0; v < 4; ++v) yv[u][rb][v] = row[u][v][rr[rb]];
+            }
+        for (int b0 = 0; b0 < nx; b0 += 16) {
+            double av[2][4], bv[4][RB];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int bb = min(b0 + 4 * k + lg, nx - 1);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) av[u][k] = O.Lb[(size_t)bb * T.n + cb + min(t0 + 64 * u + li, nt - 1)];
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) bv[k][rb] = lc[(size_t)bb * nrhs + rr[rb]];
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (b0 + 4 * k >= nx) break;  // uniform
+                const bool ok = b0 + 4 * k + lg < nx;
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb)
+                        Y[u][rb] = __builtin_amdgcn_mfma_f64_16x16x4f64(ok ? av[u][k] : 0.0, ok ? bv[k][rb] : 0.0, Y[u][rb], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (t0 + 64 * u + 4 * v + lg < nt && 16 * rb + li < nrhs)
+                        row[u][v][16 * rb + li] = yv[u][rb][v] + Y[u][rb][v];
     }
 }
 
@@ -3611,7 +3685,10 @@ hipError_t launch_matvec(const DevTree &T, const DevOp &O, const double *x, doub
         if (timer) (void)hipEventRecord(timer->p2p_stop, st);
         if (e != hipSuccess || !split) return e;
         if ((e = hipStreamWaitEvent(st, fork->joined, 0)) != hipSuccess) return e;
-        hipLaunchKernelGGL(l2p_add_kernel, dim3(T.nleaf), dim3(256), sizeof(double) * O.nx * nrhs, st, T, O, y, nrhs);
+        if (nrhs <= 16)
+            hipLaunchKernelGGL((l2p_add_kernel<1>), dim3(T.nleaf), dim3(256), 0, st, T, O, y, nrhs);
+        else
+            hipLaunchKernelGGL((l2p_add_kernel<2>), dim3(T.nleaf), dim3(256), 0, st, T, O, y, nrhs);
         return hipGetLastError();
     }
     switch (O.kind) {
