@@ -1149,14 +1149,14 @@ hipError_t cg_run(dwfmm_op op, double lambda, const double *b, double *x, int nr
             for (int c = 0; c < nrhs; ++c) active |= hstate[c] == 0;
             if (!active) break;
         }
-        if ((e = matvecA(p, q)) != hipSuccess) return e;
-        if ((e = launch_dot(p, q, T.n, nrhs, op->partial, scal + 2 * nrhs, st)) != hipSuccess) return e;
+        if ((e = launch_matvec(T, op->D, p, q, nrhs, 3, precision, st, nullptr, &op->fork)) != hipSuccess) return e;
+        if ((e = lambda != 0.0 ? launch_cg_cols_ridge(q, p, lambda, T.n, nrhs, op->partial, scal + 2 * nrhs, st)
+                               : launch_dot(p, q, T.n, nrhs, op->partial, scal + 2 * nrhs, st)) != hipSuccess)
+            return e;
         hipLaunchKernelGGL(cg_alpha_kernel, dim3(nb), dim3(64), 0, st, scal, state, nrhs);
         // x += a p ; r -= a q  (a = 0 for inactive columns)
-        hipLaunchKernelGGL(axpy_kernel, dim3(kEwBlocks), dim3(256), 0, st, x, x, p, scal, 4, 1.0, state, 0, total, nrhs);
-        hipLaunchKernelGGL(axpy_kernel, dim3(kEwBlocks), dim3(256), 0, st, r, r, q, scal, 4, -1.0, state, 0, total,
-                           nrhs);
-        if ((e = launch_dot(r, r, T.n, nrhs, op->partial, scal + 3 * nrhs, st)) != hipSuccess) return e;
+        if ((e = launch_cg_cols_step(x, r, p, q, scal + 4 * nrhs, T.n, nrhs, op->partial, scal + 3 * nrhs, st)) != hipSuccess)
+            return e;
         hipLaunchKernelGGL(cg_beta_kernel, dim3(nb), dim3(64), 0, st, scal, state, nrhs);
         // p = r + beta p on active columns
         hipLaunchKernelGGL(axpy_kernel, dim3(kEwBlocks), dim3(256), 0, st, p, r, p, scal, 5, 1.0, state, 1, total,

@@ -207,6 +207,12 @@ hipError_t launch_batch_m2l(const BatchPlan &P, const BatchLaunch &L, hipStream_
 constexpr int kDotBlocks = 1024;
 hipError_t launch_dot(const double *a, const double *b, int n, int nrhs, double *partial, double *out,
                       hipStream_t stream);
+// Several-rhs CG passes with the inner product that follows (in launch_dot's order):
+// q += lambda p, out = p.q;  x += a p, r -= a q, out = r.r (a, out per column)
+hipError_t launch_cg_cols_ridge(double *q, const double *p, double lambda, int n, int nrhs, double *partial, double *out,
+                                hipStream_t stream);
+hipError_t launch_cg_cols_step(double *x, double *r, const double *p, const double *q, const double *a, int n, int nrhs,
+                               double *partial, double *out, hipStream_t stream);
 
 // ---- FP64 CG for problems with one right-hand side, any number of them per launch ----
 // One problem of a CG launch: CG on (K~ + lambda I) x = b, with A p (or A x) already in q when
