@@ -169,7 +169,7 @@ dwfmm_status dwfmm_build_tree_ex(const double *points, int64_t n, int32_t d, con
  * every cluster and the interpolation nodes of every box, and allocates the
  * workspace for opts->max_nrhs right-hand sides.  The operator keeps a reference
  * on the tree.  Synchronises `stream`.  n_x <= 128 and n_x * d (rounded up to a
- * multiple of 4) <= 3072; above n_x = 64 the coupling runs on the general kernel.
+ * multiple of 4) <= 3072.
  * Errors: E_INVALID (bad kernel, q, opts, index set too large), E_NOMEM, E_HIP.  */
 dwfmm_status dwfmm_fmm_create(dwfmm_tree tree, dwfmm_kernel kernel, double q, const dwfmm_opts *opts,
                               void *stream, dwfmm_op *out);
@@ -177,8 +177,7 @@ dwfmm_status dwfmm_fmm_create(dwfmm_tree tree, dwfmm_kernel kernel, double q, co
 /* y = K~ x (Sec 5.2 eq. (LowRankBlock) on the farfield, kernel entries on the
  * nearfield), in the operator's precision.  x, y: device N x nrhs, distinct.
  * 1 <= nrhs <= max_nrhs.  Asynchronous on `stream`; allocates nothing.  On the
- * MFMA nearfield paths (one rhs, or up to 32 with leaves of at most 128 points and
- * d <= 32) the farfield (M2M, M2L, L2L) runs on the operator's own side stream
+ * MFMA nearfield paths (radial kernels, d <= 32; above d = 28 at most 16 rhs) the farfield (M2M, M2L, L2L) runs on the operator's own side stream
  * beside the nearfield, ordered after the P2M on `stream` and joined back into
  * `stream` before the final combine or L2P, so the result is ordered on `stream`
  * as usual.  The
