@@ -141,6 +141,7 @@ struct dwfmm_op_s {
     HostBasis B;
     DevOp D{};
     Arena arena;
+    std::vector<double> node_shift;  // what nodesT and nnorm are relative to (here and in evaluation plans)
     int precision = 0, max_nrhs = 1, check_every = 1, ir_max_outer = 30, ir_max_inner = 0;
     double ir_inner_rtol = 0.0;
     void (*progress)(void *, int32_t, int32_t, const double *) = nullptr;
@@ -524,6 +525,44 @@ static std::vector<int64_t> near_tile_offsets(const HostTree &H)
     return off;
 }
 
+// What the MFMA couplings' node coordinates are taken relative to.  They form squared distances as
+// |x|^2 + |y|^2 - 2 x.y, whose rounding is that of the norms, so the nodes of a cloud away from the origin
+// are shifted to the midpoint of its root box.  A cloud whose largest norm is within four half diagonals of
+// that box stays as it is: the shift would gain it less than a digit (norms enter squared), and it keeps the
+// results it has.
+static std::vector<double> node_shift(const HostTree &H)
+{
+    std::vector<double> mid(H.d);
+    double far2 = 0.0, half2 = 0.0;
+    for (int k = 0; k < H.d; ++k) {
+        const double lo = H.lo[k], hi = H.hi[k];
+        mid[k] = 0.5 * lo + 0.5 * hi;
+        far2 += std::max(lo * lo, hi * hi);
+        half2 += 0.25 * (hi - lo) * (hi - lo);
+    }
+    if (!(far2 > 16.0 * half2)) mid.assign(H.d, 0.0);
+    return mid;
+}
+
+// Axis-major zero-padded copy of the nodes for the MFMA couplings, relative to shift, and its squared norms.
+static void coupling_nodes(const HostTree &H, int nx, const std::vector<double> &nodes, const std::vector<double> &shift,
+                           std::vector<double> &nodesT, std::vector<double> &nnorm)
+{
+    const int dk = (H.d + 3) / 4 * 4, nxp = (nx + 15) / 16 * 16;
+    nodesT.assign((size_t)H.ncl * dk * nxp, 0.0);
+    nnorm.assign((size_t)H.ncl * nxp, 0.0);
+    for (int64_t c = 0; c < H.ncl; ++c)
+        for (int a = 0; a < nx; ++a) {
+            double s = 0.0;
+            for (int k = 0; k < H.d; ++k) {
+                const double v = nodes[((size_t)c * nx + a) * H.d + k] - shift[k];
+                nodesT[((size_t)c * dk + k) * nxp + a] = v;
+                s += v * v;
+            }
+            nnorm[(size_t)c * nxp + a] = s;
+        }
+}
+
 // Whether one-rhs CG on this tree reads its state one iteration late (cg_run1): worth it while the
 // matvec it may waste costs less than the ~20 us gaps of the ten or more iterations it saves, so up to
 // about 150 us of nearfield (1.1e-12 s an evaluated entry).
@@ -588,19 +627,10 @@ extern "C" dwfmm_status dwfmm_fmm_create(dwfmm_tree tree, dwfmm_kernel kernel, d
         for (int a = 0; a < nx; ++a)
             for (int k = 0; k < H.d; ++k)
                 nodes_p[((size_t)c * nx + a) * dp + k] = nodes[((size_t)c * nx + a) * H.d + k];
-    // axis-major zero-padded copy for the MFMA coupling kernel, and squared node norms
-    const int dk = (H.d + 3) / 4 * 4, nxp = (nx + 15) / 16 * 16;
-    std::vector<double> nodesT((size_t)H.ncl * dk * nxp, 0.0), nnorm((size_t)H.ncl * nxp, 0.0);
-    for (int64_t c = 0; c < H.ncl; ++c)
-        for (int a = 0; a < nx; ++a) {
-            double s = 0.0;
-            for (int k = 0; k < H.d; ++k) {
-                const double v = nodes[((size_t)c * nx + a) * H.d + k];
-                nodesT[((size_t)c * dk + k) * nxp + a] = v;
-                s += v * v;
-            }
-            nnorm[(size_t)c * nxp + a] = s;
-        }
+    const int nxp = (nx + 15) / 16 * 16;
+    std::vector<double> nodesT, nnorm;
+    op->node_shift = node_shift(H);
+    coupling_nodes(H, nx, nodes, op->node_shift, nodesT, nnorm);
     transfer_matrices(H, B, E);
     // Legendre slots (axis, degree >= 1) and, per basis function, the slots whose product it is
     std::vector<int32_t> leg_axis, leg_deg;
@@ -2607,19 +2637,9 @@ extern "C" dwfmm_status dwfmm_eval_create(dwfmm_op op, const double *targets, in
         for (int a = 0; a < nx; ++a)
             for (int k = 0; k < d; ++k)
                 nodes_p[((size_t)c * nx + a) * dp + k] = nodes[((size_t)c * nx + a) * d + k];
-    // axis-major zero-padded nodes and squared node norms for the MFMA coupling (as for the operator)
-    const int dkx = (d + 3) / 4 * 4, nxp = op->D.nxp;
-    std::vector<double> nodesT((size_t)H.ncl * dkx * nxp, 0.0), nnorm((size_t)H.ncl * nxp, 0.0);
-    for (int64_t c = 0; c < H.ncl; ++c)
-        for (int a = 0; a < nx; ++a) {
-            double sq = 0.0;
-            for (int k = 0; k < d; ++k) {
-                const double v = nodes[((size_t)c * nx + a) * d + k];
-                nodesT[((size_t)c * dkx + k) * nxp + a] = v;
-                sq += v * v;
-            }
-            nnorm[(size_t)c * nxp + a] = sq;
-        }
+    // (as for the operator; both sides of the coupling take the source's shift)
+    std::vector<double> nodesT, nnorm;
+    coupling_nodes(H, nx, nodes, op->node_shift, nodesT, nnorm);
     transfer_matrices(H, op->B, E);
 
     auto up = [&](auto **dst, const auto &v) { return ev->arena.upload(dst, v, st); };

@@ -55,8 +55,8 @@ struct DevOp {
     __bf16 *xtb;                  // [n][nrhs] the same charges rounded to BF16 through FP32 (max_nrhs > 1)
     double *M, *L;                // [ncl][nx][max_nrhs] moments and locals
     int nxp;                      // nx rounded up to a multiple of 16
-    const double *nodesT;         // [ncl][dk][nxp] nodes, axis-major, zero padded (dk = d rounded up to 4)
-    const double *nnorm;          // [ncl][nxp] squared norms of the nodes, zero padded
+    const double *nodesT;         // [ncl][dk][nxp] nodes (shifted: node_shift), axis-major, zero padded (dk = d rounded up to 4)
+    const double *nnorm;          // [ncl][nxp] their squared norms, zero padded
     double *rowbuf;               // [nleaf][128] owner-side nearfield row sums (one rhs)
     double *colbuf;               // [nblk][128] column sums of owned blocks (one rhs)
     // Gaussian only: every nearfield exponent |x - c|^2 / ell, |y - c|^2 / ell, 2 (x - c).(y - c) / ell

@@ -2635,8 +2635,29 @@ struct m2l_types<0> {
     typedef dbl4 V;
 };
 
-// O/Os: target and source side (the same operator for the matvec; T's lists name source clusters).
-template <int KIND, int DK, int PREC>
+// Node coordinates x (lane (a + 16 g): coordinates 4 kc + g of node a) made relative to the target
+// cluster's first node o; their squared norm, in every lane of the node.  The boxes of a far pair are no
+// larger than about their distance, so the norms of the Gram form are then of the size of r^2 and its
+// rounding is that of the differences.  With the norms of the cloud's coordinates a pair at a tenth of
+// its diameter lost two digits, and clouds away from the origin more (1e-5 at 1e4 from it).  It costs 2 %
+// where the coupling is half the work (N = 1e5, d = 20, n_x = 97, 25 rhs: 9.31 -> 9.52 ms a matvec).
+template <int NKC>
+__device__ __forceinline__ double shift_nodes(double (&x)[NKC], const double (&o)[NKC])
+{
+    double s = 0.0;
+#pragma unroll
+    for (int kc = 0; kc < NKC; ++kc) {
+        x[kc] -= o[kc];
+        s = fma(x[kc], x[kc], s);
+    }
+    s += __shfl_xor(s, 16, 64);
+    s += __shfl_xor(s, 32, 64);
+    return s;
+}
+
+// O/Os: target and source side (the same operator for the matvec; T's lists name source clusters).  SHIFT
+// (FP64): nodes relative to the target cluster's first one.
+template <int KIND, int DK, int PREC, bool SHIFT>
 __device__ __forceinline__ void m2l_mrhs_body(const DevTree &T, const DevOp &O, const DevOp &Os, int first, int nrhs)
 {
     typedef typename m2l_types<PREC>::T R;
@@ -2653,14 +2674,20 @@ __device__ __forceinline__ void m2l_mrhs_body(const DevTree &T, const DevOp &O, 
     const double inv_ell = 1.0 / O.ell;
     // target nodes as the B operand: lane (a + 16 g) holds coordinate 4 kc + g of node 16 rt + a
     const double *tnode = O.nodesT + (size_t)c * DK * nxp;
-    R Bt[2][NKC], tn[2];
+    R Bt[2][NKC], tn[2], tc[NKC];
     V4 Y[2][2];
+    static_assert(!SHIFT || !LP);
+    if constexpr (SHIFT) {
+#pragma unroll
+        for (int kc = 0; kc < NKC; ++kc) tc[kc] = tnode[(4 * kc + lg) * nxp];
+    }
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt) {
         const int a = rt < nxt ? 16 * rt + li : li;
 #pragma unroll
         for (int kc = 0; kc < NKC; ++kc) Bt[rt][kc] = (R)tnode[(4 * kc + lg) * nxp + a];
-        tn[rt] = (R)O.nnorm[(size_t)c * nxp + a];
+        if constexpr (SHIFT) tn[rt] = shift_nodes(Bt[rt], tc);
+        else tn[rt] = (R)O.nnorm[(size_t)c * nxp + a];
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb) Y[rt][rb] = V4{0, 0, 0, 0};
     }
@@ -2674,11 +2701,14 @@ __device__ __forceinline__ void m2l_mrhs_body(const DevTree &T, const DevOp &O, 
             R Af[NKC];
 #pragma unroll
             for (int kc = 0; kc < NKC; ++kc) Af[kc] = (R)snode[(4 * kc + lg) * nxp + 16 * ct + li];
+            R sa = 0;
+            if constexpr (SHIFT) sa = shift_nodes(Af, tc);
             R sn[4], Mq[2][4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int b = LP ? 16 * ct + 4 * lg + e : 16 * ct + 4 * e + lg;  // source node of element e
-                sn[e] = (R)Os.nnorm[(size_t)s * nxp + b];
+                if constexpr (SHIFT) sn[e] = __shfl(sa, 4 * e + lg, 64);
+                else sn[e] = (R)Os.nnorm[(size_t)s * nxp + b];
 #pragma unroll
                 for (int rb = 0; rb < 2; ++rb) {
                     // B operand of chunk e: lane (r + 16 g) holds m_s[source node][rhs 16 rb + r]
@@ -2760,13 +2790,13 @@ __device__ __forceinline__ void m2l_mrhs_body(const DevTree &T, const DevOp &O, 
 template <int KIND, int DK, int PREC>
 __global__ __launch_bounds__(256) void m2l_mrhs_kernel(DevTree T, DevOp O, int first, int nrhs)
 {
-    m2l_mrhs_body<KIND, DK, PREC>(T, O, O, first, nrhs);
+    m2l_mrhs_body<KIND, DK, PREC, false>(T, O, O, first, nrhs);
 }
 
 template <int KIND, int DK>
 __global__ __launch_bounds__(256) void m2l_mrhs_cross_kernel(DevTree T, DevOp Ot, DevOp Os, int first, int nrhs)
 {
-    m2l_mrhs_body<KIND, DK, 0>(T, Ot, Os, first, nrhs);
+    m2l_mrhs_body<KIND, DK, 0, true>(T, Ot, Os, first, nrhs);
 }
 
 template <int KIND>
@@ -2789,11 +2819,13 @@ void launch_m2l_mrhs_cross_k(const DevTree &T, const DevOp &Ot, const DevOp &Os,
 // wave w holds the target node tiles w and w + 4 as the Gram's B operand, so the four waves share
 // every source tile (read from L2, no staging, no barrier) and each local is summed by one lane
 // group in list order.  RB as in the several-rhs nearfield: the kernel tile is the A operand of the
-// apply MFMA; RB = 0 (one rhs) sums on the vector ALU.  Bound by the FP64 pipe; against the general
+// apply MFMA; RB = 0 (one rhs) sums on the vector ALU.  Bound by the FP64 pipe (four waves per SIMD up
+// to d = 20, by the attribute: the target frame's registers would leave three, 2 % slower); against the general
 // kernel (one thread per coupling entry, S through LDS) at N = 1e5, d = 20, n_x = 97, 25 rhs:
 // 35.8 -> 4.6 ms.
 template <int KIND, int DK, int RB>
-__global__ __launch_bounds__(256) void m2l_wide_kernel(DevTree T, DevOp O, DevOp Os, int first, int nrhs)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DK <= 20 ? 4 : 1, 8)))
+void m2l_wide_kernel(DevTree T, DevOp O, DevOp Os, int first, int nrhs)
 {
     constexpr int NKC = DK / 4;
     const int c = first + blockIdx.x;
@@ -2805,30 +2837,32 @@ __global__ __launch_bounds__(256) void m2l_wide_kernel(DevTree T, DevOp O, DevOp
     const double inv_ell = 1.0 / O.ell;
     const bool two = w + 4 < nxt;  // uniform over the wave
     const double *tnode = O.nodesT + (size_t)c * DK * nxp;
-    double Bt[2][NKC], tn[2], racc[2] = {0.0, 0.0};
+    double Bt[2][NKC], tn[2], tc[NKC], racc[2] = {0.0, 0.0};
     dbl4 Y[2][RB == 0 ? 1 : RB];
+#pragma unroll
+    for (int kc = 0; kc < NKC; ++kc) tc[kc] = tnode[(4 * kc + lg) * nxp];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         const int a = 16 * (two ? w + 4 * u : w) + li;
 #pragma unroll
         for (int kc = 0; kc < NKC; ++kc) Bt[u][kc] = tnode[(4 * kc + lg) * nxp + a];
-        tn[u] = O.nnorm[(size_t)c * nxp + a];
+        tn[u] = shift_nodes(Bt[u], tc);
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) Y[u][rb] = dbl4{0.0, 0.0, 0.0, 0.0};
     }
     for (int f = f0; f < f1; ++f) {
         const int s = T.Fsrc[f];
         const double *snode = Os.nodesT + (size_t)s * DK * nxp;
-        const double *snorm = Os.nnorm + (size_t)s * nxp;
         const double *ms = Os.M + (size_t)s * nx * nrhs;
         for (int ct = 0; ct < nxt; ++ct) {
             double Af[NKC], sn[4], Mq[RB == 0 ? 1 : RB][4];
 #pragma unroll
             for (int kc = 0; kc < NKC; ++kc) Af[kc] = snode[(4 * kc + lg) * nxp + 16 * ct + li];
+            const double sa = shift_nodes(Af, tc);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int b = 16 * ct + 4 * e + lg;  // source node of element e; padding nodes carry moment 0
-                sn[e] = snorm[b];
+                sn[e] = __shfl(sa, 4 * e + lg, 64);
                 const int bb = b < nx ? b : nx - 1;
                 if constexpr (RB == 0) {
                     const double m = ms[bb];
@@ -2849,7 +2883,11 @@ __global__ __launch_bounds__(256) void m2l_wide_kernel(DevTree T, DevOp O, DevOp
                 for (int kc = 0; kc < NKC; ++kc) G = __builtin_amdgcn_mfma_f64_16x16x4f64(Af[kc], Bt[u][kc], G, 0, 0, 0);
                 double Kv[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) Kv[e] = kernel_fast<KIND>(fmax(fma(-2.0, G[e], tn[u] + sn[e]), 0.0), inv_ell);
+                for (int e = 0; e < 4; ++e) {
+                    double r2 = fma(-2.0, G[e], tn[u] + sn[e]);
+                    if constexpr (KIND == 1) r2 = fmax(r2, 0.0);  // (the others clamp it themselves)
+                    Kv[e] = kernel_fast<KIND>(r2, inv_ell);
+                }
                 if constexpr (RB == 0) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) racc[u] = fma(Kv[e], Mq[0][e], racc[u]);
