@@ -525,6 +525,13 @@ static std::vector<int64_t> near_tile_offsets(const HostTree &H)
     return off;
 }
 
+// Whether the Gram form of the nearfield of pieces (Matern in range, split Gaussian) rounds close pairs
+// within 1e-13, reach2 bounding every squared distance to the shift it forms: see mrhs_near in kernels.hip.
+static bool gram_close(int kind, double reach2, double ell)
+{
+    return kind == DWFMM_GAUSSIAN ? reach2 / ell <= 300.0 : std::sqrt(reach2) / ell <= 24.0;
+}
+
 // What the MFMA couplings' node coordinates are taken relative to.  They form squared distances as
 // |x|^2 + |y|^2 - 2 x.y, whose rounding is that of the norms, so the nodes of a cloud away from the origin
 // are shifted to the midpoint of its root box.  A cloud whose largest norm is within four half diagonals of
@@ -732,6 +739,7 @@ extern "C" dwfmm_status dwfmm_fmm_create(dwfmm_tree tree, dwfmm_kernel kernel, d
                         std::sqrt(tree->near_reach2) * (1.7320508075688772 * 1.4426950408889634) / kernel.ell <= 1000.0;
     D.exp_in_range = kernel.kind == DWFMM_EXPONENTIAL &&
                      std::sqrt(tree->near_reach2) * 1.4426950408889634 / kernel.ell <= 1000.0;
+    D.gram_close = gram_close(kernel.kind, tree->near_reach2, kernel.ell);
     D.nx = nx;
     D.max_nrhs = o.max_nrhs;
     D.nodes = dnodes;
@@ -2728,6 +2736,7 @@ extern "C" dwfmm_status dwfmm_eval_create(dwfmm_op op, const double *targets, in
         O.matern_in_range = O.kind == DWFMM_MATERN32 &&
                             std::sqrt(bmax2) * (1.7320508075688772 * 1.4426950408889634) / O.ell <= 1000.0;
         O.exp_in_range = O.kind == DWFMM_EXPONENTIAL && std::sqrt(bmax2) * 1.4426950408889634 / O.ell <= 1000.0;
+        O.gram_close = gram_close(O.kind, bmax2, O.ell);
     }
     if ((e = hipMemsetAsync(dL, 0, sizeof(double) * H.ncl * nx * R, st)) != hipSuccess ||
         (e = launch_basis(D, nx, dclo, dcsc, dcoff, op->b_lidx, op->b_nnz, op->b_Vinv, op->b_nleg, op->b_la, op->b_ld,

@@ -68,6 +68,7 @@ struct DevOp {
     // bound), so the FP64 nearfield's 2^-s log2(e) needs no underflow clamp
     int matern_in_range;
     int exp_in_range;             // exponential only: the same for max|x - y| / ell log2(e)
+    int gram_close;               // Matern: the same bound within 24 ell; Gaussian: its square within 300 ell (mrhs_near)
     // Power of two 2^-e with every centred nearfield coordinate (a point minus its target leaf's
     // midpoint) at most 1 in magnitude after scaling (e from the host's reach bound): the BF16
     // several-rhs nearfield forms its FP16 Gram operands from the scaled coordinates

@@ -1262,7 +1262,7 @@ constexpr int kSX64 = kSymLeaf + 16;
 // kernels in range and the split Gaussian where it leaves as many workgroups per CU (160 KB) as the
 // kernel has without it, at most the four that its registers allow.  (The square operator's Matern
 // runs the clamped kernel here: see kExpInRange.)
-constexpr int mrhs_lds(int dk, int rb) { return 8 * (dk * (kSX64 + 1) + kSymLeaf * (rb == 0 ? 3 : 16 * rb + 2)) + 4 * (2 * kSymSeg + kSymLeaf + 8); }
+constexpr int mrhs_lds(int dk, int rb) { return 8 * (dk * (kSX64 + 1) + kSymLeaf * (rb == 0 ? 3 : 16 * rb + 2)) + 4 * (2 * kSymSeg + 2 * kSymLeaf + 8); }
 constexpr int mrhs_wgs(int lds) { return 163840 / lds < 4 ? 163840 / lds : 4; }
 // The split Gaussian of the square operator keeps the polynomial, since its matvec closes the
 // refinement solves of the reduced precisions (a last bit there moved their alpha by 5e-9).
@@ -1273,43 +1273,67 @@ constexpr bool mrhs_tab()
            mrhs_wgs(mrhs_lds(DK, RB) + 8 * kExp2Size) == mrhs_wgs(mrhs_lds(DK, RB));
 }
 
-// The squared distance of target i (of tree T, shifted by cen and scaled by csc) and staged source
-// column j from the coordinate differences themselves.  With the Gram form the rounding of |x|^2 + |y|^2 - 2 x.y is
-// that of the norms, which the exponential kernel's sqrt turns into an error of the kernel value
-// for nearly coincident points; the caller takes this form there (1e-4 of the norms and below: rare
-// in more than two dimensions, and the error it leaves elsewhere is 5e-14 of the points' distance
-// from the shift over ell).
+// Distances of the cross form.  With the Gram form the rounding of |x|^2 + |y|^2 - 2 x.y is that of the
+// norms N (relative to the shift), which for close points is an error of the kernel value that grows with
+// rho = sqrt(N) / ell: eps rho for the exponential's square root of a tiny r^2 and 1.5 eps rho^2 for Matern,
+// eps rho^2 for the Gaussian (direct or split).  So
+//   - r^2 < kNear N: the differences of the coordinates instead, for the exponential (no cost: d = 6,
+//     1e5 sources, 5e4 targets 1.25 ms with 1e-4 and 1e-2 alike) and the clamped kernels.  What is left is
+//     eps rho exp(-sqrt(kNear) rho) / (2 sqrt(kNear)), 0.8 eps / kNear for Matern, 0.4 eps / kNear for
+//     the Gaussian: 1e-14 and less at any rho;
+//   - Matern in range and the split Gaussian have no such branch (it cost Matern 5 to 9 %) and are taken only
+//     where their error stays under 1e-13: rho <= 24, rho^2 <= 300 (gram_close);
+//   - the clamped kernels at d <= 4: the differences throughout (d = 4 Matern 1.01 ms, with the branch 1.06).
+template <int KIND, int DK, bool CROSS>
+constexpr bool mrhs_diff() { return CROSS && DK == 4 && KIND <= 2; }
+template <int KIND, int DK, bool CROSS>
+constexpr double mrhs_near()
+{
+    return !CROSS || mrhs_diff<KIND, DK, CROSS>() || KIND == kGaussSplit || KIND == kMaternInRange ? 0.0 : 1e-2;
+}
+
+// |x_i - y_p|^2 of target i and source p from their coordinates.
 template <int DK>
-__device__ __forceinline__ double r2_direct(const DevTree &T, const double *cen, double csc, int i, const double *sX, int j)
+__device__ __forceinline__ double r2_direct(const DevTree &T, const DevTree &Ts, int i, int p)
 {
     double r2 = 0.0;
 #pragma unroll 1  // (unrolled, its loads cost the tile loop a wave per SIMD)
     for (int k = 0; k < DK; ++k) {
-        const double t = csc * (T.Xs[(size_t)k * T.n + i] - cen[k]) - sX[k * kSX64 + j];
+        const double t = T.Xs[(size_t)k * T.n + i] - Ts.Xs[(size_t)k * Ts.n + p];
         r2 = fma(t, t, r2);
     }
     return r2;
 }
 
-// near_i (cross form, exponential kernel): the tree positions of this lane's two targets.
+// near_i, sP (where mrhs_near): the tree positions of this lane's two targets, the staged columns' points;
+// tx (where mrhs_diff): the coordinates of the two targets, sX then holding the sources' as they are.
 template <int KIND, int DK, int RB, bool DIAG, bool CROSS>
 __device__ __forceinline__ void mrhs_block(const double (&Bt)[2][DK / 4], const double (&tn)[2], dbl4 (&Y)[2][RB == 0 ? 1 : RB],
                                            double (&racc)[2], const double *sX, const double *sN, const double *sQ,
                                            int ns, int ntiles, int w, int li, int lg, double inv_ell,
-                                           const DevTree &T, const double *cen, const int (&near_i)[2],
-                                           const uint2 *tab)
+                                           const DevTree &T, const DevTree &Ts, const int (&near_i)[2],
+                                           const int32_t *sP, const double (&tx)[2][4], const uint2 *tab)
 {
     constexpr int NKC = DK / 4;
-    constexpr bool kTab = mrhs_tab<KIND, DK, RB, CROSS>();
+    constexpr bool kTab = mrhs_tab<KIND, DK, RB, CROSS>(), kDiff = mrhs_diff<KIND, DK, CROSS>();
+    constexpr double kNear = mrhs_near<KIND, DK, CROSS>();
+    // scale of the staged coordinates
+    const double csc = KIND == kExpInRange ? 1.4426950408889634 * inv_ell : 1.0;
     const int rt[2] = {w, w + 4};
     const int nct = (ns + 15) / 16;
     for (int ct = 0; ct < nct; ++ct) {
-        double Af[NKC];
+        double Af[NKC], snv[4], sx[4][4];
+        if constexpr (kDiff) {
 #pragma unroll
-        for (int kc = 0; kc < NKC; ++kc) Af[kc] = sX[(4 * kc + lg) * kSX64 + 16 * ct + li];
-        double snv[4];
+            for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) snv[v] = sN[16 * ct + 4 * v + lg];
+                for (int v = 0; v < 4; ++v) sx[k][v] = sX[k * kSX64 + 16 * ct + 4 * v + lg];
+        } else {
+#pragma unroll
+            for (int kc = 0; kc < NKC; ++kc) Af[kc] = sX[(4 * kc + lg) * kSX64 + 16 * ct + li];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) snv[v] = sN[16 * ct + 4 * v + lg];
+        }
         double Qf[RB == 0 ? 1 : RB][4];
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
@@ -1331,8 +1355,10 @@ __device__ __forceinline__ void mrhs_block(const double (&Bt)[2][DK / 4], const 
                 G = dbl4{snv[0], snv[1], snv[2], snv[3]};
             else
                 G = dbl4{0.0, 0.0, 0.0, 0.0};
+            if constexpr (!kDiff) {
 #pragma unroll
-            for (int kc = 0; kc < NKC; ++kc) G = __builtin_amdgcn_mfma_f64_16x16x4f64(Af[kc], Bt[u][kc], G, 0, 0, 0);
+                for (int kc = 0; kc < NKC; ++kc) G = __builtin_amdgcn_mfma_f64_16x16x4f64(Af[kc], Bt[u][kc], G, 0, 0, 0);
+            }
             double Kv[4];
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -1340,15 +1366,25 @@ __device__ __forceinline__ void mrhs_block(const double (&Bt)[2][DK / 4], const 
                     Kv[v] = kTab ? exp2_tab(G[v], tab) : exp2_bounded(G[v]);
                 } else {
                     // (the kernels in range: the coordinates carry their scale, so r2 is s^2)
-                    double r2 = fma(-2.0, G[v], tn[u] + snv[v]);
-                    if constexpr (KIND != kExpInRange && KIND != kMaternInRange) r2 = fmax(r2, 0.0);
+                    double r2;
+                    if constexpr (kDiff) {
+                        r2 = 0.0;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            const double t = tx[u][k] - sx[k][v];
+                            r2 = fma(t, t, r2);
+                        }
+                    } else {
+                        r2 = fma(-2.0, G[v], tn[u] + snv[v]);
+                        if constexpr (KIND != kExpInRange && KIND != kMaternInRange) r2 = fmax(r2, 0.0);
+                    }
                     if constexpr (DIAG) {
                         if (16 * rt[u] + li == 16 * ct + 4 * v + lg) r2 = 0.0;
                     }
-                    if constexpr (CROSS && (KIND == 2 || KIND == kExpInRange)) {
-                        if (r2 <= 1e-4 * (tn[u] + snv[v]))
-                            r2 = r2_direct<DK>(T, cen, KIND == kExpInRange ? 1.4426950408889634 * inv_ell : 1.0, near_i[u], sX,
-                                               16 * ct + 4 * v + lg);
+                    if constexpr (kNear > 0.0) {
+                        // (never a padding column: it sits on the shift, r2 is tn)
+                        if (r2 < kNear * (tn[u] + snv[v]))
+                            r2 = csc * csc * r2_direct<DK>(T, Ts, near_i[u], sP[16 * ct + 4 * v + lg]);
                     }
                     if constexpr (KIND == kExpInRange)
                         Kv[v] = exponential_s2<kTab>(r2, tab);
@@ -1384,7 +1420,9 @@ __device__ __forceinline__ void p2p_mrhs_body(const DevTree &T, const DevOp &O, 
     __shared__ double sQ[kSymLeaf * q_stride<RB>()];  // charges [j][r]
     __shared__ double cen[DK];
     __shared__ int32_t sPre[kSymSeg + 1], sBeg[kSymSeg], colP[kSymLeaf], sDiag;
-    constexpr bool kSplit = KIND == kGaussSplit;
+    constexpr bool kSplit = KIND == kGaussSplit, kDiff = mrhs_diff<KIND, DK, CROSS>();
+    constexpr bool kNear = mrhs_near<KIND, DK, CROSS>() > 0.0;
+    __shared__ int32_t sP[kNear ? kSymLeaf : 1];  // the points of the staged columns (colP is ahead of the tiles)
     __shared__ double tF[kSplit ? kSymLeaf : 1];  // split Gaussian: row factors exp(-|x - c|^2 / ell)
     int l = T.near_order[blockIdx.x];
     if (l < 0) return;  // padding of a shorter XCD segment
@@ -1417,6 +1455,7 @@ __device__ __forceinline__ void p2p_mrhs_body(const DevTree &T, const DevOp &O, 
     double Bt[2][NKC], tn[2], racc[2] = {0.0, 0.0};
     dbl4 Y[2][RB == 0 ? 1 : RB];
     int near_i[2];
+    double tx[2][4];
     const double csc = KIND == kExpInRange ? 1.4426950408889634 * inv_ell : 1.7320508075688772 * inv_ell;
     auto scaled = [&](double v) { return KIND == kExpInRange || KIND == kMaternInRange ? csc * v : v; };
 #pragma unroll
@@ -1425,6 +1464,10 @@ __device__ __forceinline__ void p2p_mrhs_body(const DevTree &T, const DevOp &O, 
         const bool ok = i < nt;
         const int ii = cb + (ok ? i : nt - 1);
         near_i[u] = ii;
+        if constexpr (kDiff) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) tx[u][k] = T.Xs[(size_t)k * n + ii];
+        }
         double s = 0.0;
 #pragma unroll
         for (int k = 0; k < DK; ++k) {
@@ -1479,10 +1522,15 @@ __device__ __forceinline__ void p2p_mrhs_body(const DevTree &T, const DevOp &O, 
                 double s = 0.0;
 #pragma unroll
                 for (int k = 0; k < DK; ++k) {
-                    const double v = ok ? scaled(xv[k] - cen[k]) : 0.0;
-                    sX[k * kSX64 + j] = v;
-                    s = fma(v, v, s);
+                    if constexpr (kDiff) {
+                        sX[k * kSX64 + j] = ok ? xv[k] : cen[k];
+                    } else {
+                        const double v = ok ? scaled(xv[k] - cen[k]) : 0.0;
+                        sX[k * kSX64 + j] = v;
+                        s = fma(v, v, s);
+                    }
                 }
+                if constexpr (kNear) sP[j] = jj;
                 // split Gaussian: the base-2 logarithm of the column factor exp(-|y - c|^2 / ell)
                 sN[j] = kSplit ? s * (-1.4426950408889634 * inv_ell) : s;
                 if constexpr (RB == 0) sQ[j] = ok ? q1 : 0.0;
@@ -1509,7 +1557,8 @@ __device__ __forceinline__ void p2p_mrhs_body(const DevTree &T, const DevOp &O, 
                 __syncthreads();
                 stage_chunk(nt, tid);
                 __syncthreads();
-                mrhs_block<KIND, DK, RB, true, false>(Bt, tn, Y, racc, sX, sN, sQ, nt, ntiles, w, li, lg, inv_ell, T, cen, near_i, tab);
+                mrhs_block<KIND, DK, RB, true, false>(Bt, tn, Y, racc, sX, sN, sQ, nt, ntiles, w, li, lg, inv_ell, T, Ts,
+                                                      near_i, sP, tx, tab);
             }
         }
         int chunk = 0;  // the column search and coordinate staging alternate between waves 0-1 and 2-3
@@ -1560,8 +1609,8 @@ __device__ __forceinline__ void p2p_mrhs_body(const DevTree &T, const DevOp &O, 
                 __syncthreads();
                 stage_chunk(ns, sid);
                 __syncthreads();
-                mrhs_block<KIND, DK, RB, false, CROSS>(Bt, tn, Y, racc, sX, sN, sQ, ns, ntiles, w, li, lg, inv_ell, T, cen,
-                                                       near_i, tab);
+                mrhs_block<KIND, DK, RB, false, CROSS>(Bt, tn, Y, racc, sX, sN, sQ, ns, ntiles, w, li, lg, inv_ell, T, Ts,
+                                                       near_i, sP, tx, tab);
             }
         }
     }
@@ -3869,10 +3918,10 @@ hipError_t launch_pieces(const DevTree &T, const DevOp &O, const DevTree &Ts, co
 {
     switch (O.kind) {
     case 0:
-        return O.matern_in_range ? launch_pieces_k<kMaternInRange>(T, O, Ts, xs, y, nrhs, near, far, st)
+        return O.matern_in_range && O.gram_close ? launch_pieces_k<kMaternInRange>(T, O, Ts, xs, y, nrhs, near, far, st)
                                  : launch_pieces_k<0>(T, O, Ts, xs, y, nrhs, near, far, st);
     case 1:
-        return O.gauss_split ? launch_pieces_k<kGaussSplit>(T, O, Ts, xs, y, nrhs, near, far, st)
+        return O.gauss_split && O.gram_close ? launch_pieces_k<kGaussSplit>(T, O, Ts, xs, y, nrhs, near, far, st)
                              : launch_pieces_k<1>(T, O, Ts, xs, y, nrhs, near, far, st);
     default:
         return O.exp_in_range ? launch_pieces_k<kExpInRange>(T, O, Ts, xs, y, nrhs, near, far, st)
