@@ -208,12 +208,13 @@ __device__ __forceinline__ double matern_s2_tab(double s2, const uint2 *tab)
     return fma(s, e, e);
 }
 
-// e^(-r / ell) from s^2 = (r log2(e) / ell)^2, for callers whose coordinates are already scaled by
-// log2(e) / ell and that guarantee s <= 1000: the guard of matern_s2, then 2^-s (from the table if TAB).
+// e^(-r / ell) from s^2 = (r log2(e) / ell)^2 >= 1e-300, for callers whose coordinates are already scaled
+// by log2(e) / ell and that guarantee s <= 1000 and clamp s^2 (its rounding may be below zero): 2^-s (from
+// the table if TAB).
 template <bool TAB>
 __device__ __forceinline__ double exponential_s2(double s2, const uint2 *tab)
 {
-    const double t = -sqrt_pos(fabs(s2) + 1e-300);
+    const double t = -sqrt_pos(s2);
     return TAB ? exp2_tab(t, tab) : exp2_bounded(t);
 }
 
@@ -967,7 +968,8 @@ __device__ __forceinline__ void sym_block(const double (&A)[2][NKC], const doubl
                     if constexpr (is_matern<KIND>())
                         kv = matern_s2<KIND == 0>(r2);
                     else if constexpr (KIND == kExpInRange)
-                        kv = exponential_s2<true>(r2, tab);
+                        // (an MFMA result: the absolute value is free, fmax would canonicalise it first)
+                        kv = exponential_s2<true>(NK ? fabs(r2) + 1e-300 : fmax(r2, 1e-300), tab);
                     else
                         kv = kernel_fast<KIND>(r2, inv_ell);
                 }
@@ -1111,7 +1113,21 @@ __device__ __forceinline__ void p2p_sym_body(const DevTree &T, const DevOp &O, i
             sN[nb + j] = bfac;
             sQ[j] = ok ? q * bfac : 0.0;
         } else {
-            sN[nb + j] = s;
+            // Exponential: minus the value that the tile's chain from |y|^2 reaches for y itself, which is
+            // |y|^2 but for its roundings, so that r^2 of repeated points is zero (with the norms in the
+            // Gram operands it is).  The square root makes 1e-8 of a rounding there, 2e-6 at a length scale
+            // of a fiftieth of the points' distance.  The second chain costs 2 % at d = 20 (N = 3e5: 2.29 ->
+            // 2.34 ms), nothing at the other d; |x|^2 added to the tile instead cost 3 to 5 % at d <= 12.
+            double t = s;
+            if constexpr (KIND == 2 || KIND == kExpInRange) {
+#pragma unroll
+                for (int k = 0; k < DK; ++k) {
+                    const double v = sX[k * kSymLeaf + j];
+                    t = fma(-2.0 * v, v, t);
+                }
+                t = -t;
+            }
+            sN[nb + j] = t;
             sQ[j] = ok ? q : 0.0;
             if (nk) {
                 sX[T.d * kSymLeaf + j] = 1.0;
@@ -1387,7 +1403,7 @@ __device__ __forceinline__ void mrhs_block(const double (&Bt)[2][DK / 4], const 
                             r2 = csc * csc * r2_direct<DK>(T, Ts, near_i[u], sP[16 * ct + 4 * v + lg]);
                     }
                     if constexpr (KIND == kExpInRange)
-                        Kv[v] = exponential_s2<kTab>(r2, tab);
+                        Kv[v] = exponential_s2<kTab>(fmax(r2, 1e-300), tab);
                     else if constexpr (KIND == kMaternInRange)
                         Kv[v] = kTab ? matern_s2_tab(r2, tab) : matern_s2<false>(r2);
                     else
