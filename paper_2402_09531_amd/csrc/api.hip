@@ -159,8 +159,8 @@ struct dwfmm_op_s {
     std::vector<KernelTimer> timers;
     size_t timers_used = 0;
     StreamFork fork;  // farfield beside the one-rhs nearfield
-    // Small problems (lookahead): the states of the last two CG iterations in pinned host memory and
-    // the events behind their copies, from the first solve on
+    // Small problems (lookahead): the states at the last two checks in pinned host memory and the events
+    // behind their copies, from the first solve on
     bool lookahead = false;
     int32_t *h_state = nullptr;
     hipEvent_t state_read[2] = {nullptr, nullptr};
@@ -570,14 +570,15 @@ static void coupling_nodes(const HostTree &H, int nx, const std::vector<double> 
         }
 }
 
-// Whether one-rhs CG on this tree reads its state one iteration late (cg_run1): worth it while the
-// matvec it may waste costs less than the ~20 us gaps of the ten or more iterations it saves, so up to
-// about 150 us of nearfield (1.1e-12 s an evaluated entry).
-static bool cg_lookahead(const dwfmm_tree t)
+// Whether one-rhs CG reads its state one iteration late (cg_run1): worth it while the matvec that this
+// wastes costs less than the ~20 us gaps it saves, one a check, ten or more iterations a solve.  So up to
+// about 150 us of matvec (1.1e-12 s an evaluated entry of the nearfield, the coupling and the transfers)
+// over the iterations between checks.
+static bool cg_lookahead(const dwfmm_tree t, int nx, int check_every)
 {
-    double work = 0.0;
+    double work = ((double)t->H.Fsrc.size() + 2.0 * (double)t->H.ncl) * nx * nx;
     for (double w : t->leaf_work) work += w;
-    return work <= 1.5e8;
+    return work * check_every <= 1.5e8;
 }
 
 extern "C" dwfmm_status dwfmm_fmm_create(dwfmm_tree tree, dwfmm_kernel kernel, double q, const dwfmm_opts *opts,
@@ -766,7 +767,7 @@ extern "C" dwfmm_status dwfmm_fmm_create(dwfmm_tree tree, dwfmm_kernel kernel, d
     op->b_Vinv = dVinv;
     op->b_nnz = nnz_max;
     op->b_nleg = (int)leg_axis.size();
-    op->lookahead = cg_lookahead(tree);
+    op->lookahead = cg_lookahead(tree, nx, o.check_every);
     if ((e = hipStreamCreateWithFlags(&op->fork.side, hipStreamNonBlocking)) != hipSuccess ||
         (e = hipEventCreateWithFlags(&op->fork.forked, hipEventDisableTiming)) != hipSuccess ||
         (e = hipEventCreateWithFlags(&op->fork.joined, hipEventDisableTiming)) != hipSuccess) {
@@ -1095,9 +1096,9 @@ hipError_t cg_run1(dwfmm_op op, double lambda, const double *b, double *x, doubl
         return e;
     hstate.assign(3, 0);
     hrr.assign(2, 0.0);
-    // Small problems read the state of iteration k - 1 while iteration k runs: the copy, the wake-up and
-    // the next launches take about 20 us, which a short matvec does not cover, for one matvec too many
-    // at the end (the vector steps of a stopped problem do nothing, so the results are the same).
+    // Small problems look at a check's state one iteration late, while that iteration runs: the copy, the
+    // wake-up and the next launches take about 20 us, which a short matvec does not cover, for one matvec
+    // too many at the end (the vector steps of a stopped problem do nothing, so the results are the same).
     if (op->lookahead && !op->progress && !op->h_state) {
         for (hipEvent_t &ev : op->state_read)
             if (!ev && (e = hipEventCreateWithFlags(&ev, hipEventDisableTiming)) != hipSuccess) return e;
@@ -1105,15 +1106,19 @@ hipError_t cg_run1(dwfmm_op op, double lambda, const double *b, double *x, doubl
     }
     const bool ahead = op->h_state && !op->progress;
     for (int k = 0; k < max_iter; ++k) {
-        if (ahead && k % op->check_every == 0) {
-            const int now = (k / op->check_every) & 1;
-            if ((e = hipMemcpyAsync(op->h_state + now, op->state, sizeof(int32_t), hipMemcpyDeviceToHost, st)) !=
-                    hipSuccess ||
-                (e = hipEventRecord(op->state_read[now], st)) != hipSuccess)
-                return e;
-            if (k >= op->check_every) {
-                if ((e = hipEventSynchronize(op->state_read[now ^ 1])) != hipSuccess) return e;
-                if (op->h_state[now ^ 1] != 0) break;
+        if (ahead) {
+            const int ce = op->check_every;
+            if (k % ce == 0) {
+                const int i = (k / ce) & 1;
+                if ((e = hipMemcpyAsync(op->h_state + i, op->state, sizeof(int32_t), hipMemcpyDeviceToHost, st)) !=
+                        hipSuccess ||
+                    (e = hipEventRecord(op->state_read[i], st)) != hipSuccess)
+                    return e;
+            }
+            if (k > 0 && (k - 1) % ce == 0) {
+                const int i = ((k - 1) / ce) & 1;
+                if ((e = hipEventSynchronize(op->state_read[i])) != hipSuccess) return e;
+                if (op->h_state[i] != 0) break;
             }
         } else if (k % op->check_every == 0) {
             if ((e = hipMemcpyAsync(hstate.data(), op->state, sizeof(int32_t), hipMemcpyDeviceToHost, st)) !=

@@ -1,0 +1,40 @@
+"""A small one-rhs solve that looks at its state one iteration late runs one matvec past the check that
+stops it, whatever the distance of the checks.
+
+With checks every 100 iterations and convergence before the first of them, it runs 101 matvecs; the same
+solve with a progress callback (state read at each check) runs 100.  The time of the first is held to 1.3
+times that of the second (1 % of matvecs, the rest is slack for timing noise; a state looked at only at
+the next check would make it 2).
+"""
+import time
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+import paper_2402_09531_amd as dw  # noqa: E402
+from paper_2402_09531_amd import workloads as W  # noqa: E402
+
+
+def test_checks_far_apart():
+    n, d = 1024, 4
+    X, b = W.points(n, d, 2.0, 7), W.dim_weights(d, 2.0)
+    Xd = torch.from_numpy(X).cuda()
+    f = torch.from_numpy(np.sin(X.sum(axis=1))[:, None].copy()).cuda()
+    ops = [dw.fmm_create(dw.build_tree(Xd, b, 64, 0.8), "matern32", 1.0, 4, check_every=100, **kw)
+           for kw in ({}, {"progress": lambda it, rr: None})]
+    best, sol = [1e9, 1e9], [None, None]
+    for _ in range(6):
+        for i, op in enumerate(ops):
+            a = torch.zeros_like(f)
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            info = dw.fmm_solve(op, 1.0, f, a, 1e-8, 5000)[0]
+            best[i] = min(best[i], time.perf_counter() - t0)
+            assert info["status"] == 0 and 0 < info["iters"] < 100
+            sol[i] = (a, info["iters"])
+    print(f"[late state] {best[0] * 1e3:.2f} ms, with a callback {best[1] * 1e3:.2f} ms", flush=True)
+    assert torch.equal(sol[0][0], sol[1][0]) and sol[0][1] == sol[1][1]
+    assert best[0] <= 1.3 * best[1]
