@@ -18,9 +18,9 @@
  *   - Objects are not thread-safe; distinct objects may be used concurrently.
  *   - The library owns all memory of a tree or operator: it is allocated in
  *     dwfmm_build_tree / dwfmm_fmm_create and freed by the destroy calls.
- *     dwfmm_fmm_matvec and dwfmm_fmm_solve allocate nothing (but for one page of
- *     pinned host memory, which the first one-rhs solve of a small problem takes
- *     for the process).
+ *     dwfmm_fmm_matvec and dwfmm_fmm_solve allocate nothing.  (The first operator
+ *     of a small problem also takes one page of pinned host memory, which the
+ *     process keeps.)
  */
 #ifndef DWFMM_H
 #define DWFMM_H
@@ -177,10 +177,11 @@ dwfmm_status dwfmm_fmm_create(dwfmm_tree tree, dwfmm_kernel kernel, double q, co
 /* y = K~ x (Sec 5.2 eq. (LowRankBlock) on the farfield, kernel entries on the
  * nearfield), in the operator's precision.  x, y: device N x nrhs, distinct.
  * 1 <= nrhs <= max_nrhs.  Asynchronous on `stream`; allocates nothing.  On the
- * MFMA nearfield paths (radial kernels, d <= 32; above d = 28 at most 16 rhs) the farfield (M2M, M2L, L2L) runs on the operator's own side stream
- * beside the nearfield, ordered after the P2M on `stream` and joined back into
- * `stream` before the final combine or L2P, so the result is ordered on `stream`
- * as usual.  The
+ * MFMA nearfield paths (radial kernels, d <= 32; above d = 28 at most 16 rhs) the
+ * farfield (M2M, M2L, L2L) runs on the operator's own side stream beside the
+ * nearfield, ordered after the P2M on `stream` and joined back into `stream`
+ * before the final combine or L2P, so the result is ordered on `stream` as usual.
+ * The
  * call may be captured into a HIP graph from `stream`; while `stream` is capturing
  * all work stays on `stream` (no library object may be destroyed during a capture:
  * the destroy calls free device memory).  Calls on one operator must not overlap (they share

@@ -77,23 +77,28 @@ struct Arena {
     } while (0)
 
 // 64 slots of 64 bytes in one page of pinned host memory, for device-to-host copies that the host
-// does not wait for at once.  One page per process, allocated by the first solve that may use it
-// (about 250 us, too much per operator) and held until the process ends; a slot is taken by an
-// operator's first such solve and given back by its destructor, from any thread.  With all slots
-// taken the caller gets NULL and does without.
+// does not wait for at once.  One page per process, allocated by the first operator that may use it
+// (about 250 us, too much per operator) and held until the process ends; a slot is taken for the time of
+// one solve, from any thread.  With all slots taken, or without a page, the caller gets NULL and does
+// without.
 class PinnedSlots {
     std::mutex m;
     unsigned char *page = nullptr;
     uint64_t used = 0;
 
 public:
-    int32_t *take()
+    bool prepare()
     {
         std::lock_guard<std::mutex> g(m);
         if (!page && hipHostMalloc((void **)&page, 4096, hipHostMallocPortable) != hipSuccess) {
             (void)hipGetLastError();
             page = nullptr;
         }
+        return page != nullptr;
+    }
+    int32_t *take()
+    {
+        std::lock_guard<std::mutex> g(m);
         if (!page || used == ~(uint64_t)0) return nullptr;
         const int k = __builtin_ctzll(~used);
         used |= (uint64_t)1 << k;
@@ -106,6 +111,20 @@ public:
     }
 };
 PinnedSlots g_pinned;
+
+// A slot for the time of one solve on st (or none); copies in flight are waited for before it goes back.
+struct PinnedSlot {
+    int32_t *const p;
+    const hipStream_t st;
+    PinnedSlot(bool want, hipStream_t s) : p(want ? g_pinned.take() : nullptr), st(s) {}
+    PinnedSlot(const PinnedSlot &) = delete;
+    ~PinnedSlot()
+    {
+        if (!p) return;
+        (void)hipStreamSynchronize(st);
+        g_pinned.give(p);
+    }
+};
 
 // coordinate rows stored per point: a multiple of 4 (the MFMA k-chunk) up to 32, of 8 beyond
 int pad_dim(int d) { return d <= 32 ? (d + 3) / 4 * 4 : (d + 7) / 8 * 8; }
@@ -159,10 +178,9 @@ struct dwfmm_op_s {
     std::vector<KernelTimer> timers;
     size_t timers_used = 0;
     StreamFork fork;  // farfield beside the one-rhs nearfield
-    // Small problems (lookahead): the states at the last two checks in pinned host memory and the events
-    // behind their copies, from the first solve on
+    // Small problems: one-rhs CG looks at its state one iteration late (cg_run1), the events behind the
+    // copies of the last two checks
     bool lookahead = false;
-    int32_t *h_state = nullptr;
     hipEvent_t state_read[2] = {nullptr, nullptr};
     int near_filled = 0;  // the BF16 nearfield tile cache holds this operator's tiles
     ~dwfmm_op_s()
@@ -170,7 +188,6 @@ struct dwfmm_op_s {
         if (fork.forked) (void)hipEventDestroy(fork.forked);
         if (fork.joined) (void)hipEventDestroy(fork.joined);
         if (fork.side) (void)hipStreamDestroy(fork.side);
-        if (h_state) g_pinned.give(h_state);
         for (hipEvent_t ev : state_read)
             if (ev) (void)hipEventDestroy(ev);
         for (auto &t : timers) {
@@ -581,8 +598,9 @@ static bool cg_lookahead(const dwfmm_tree t, int nx, int check_every)
     return work * check_every <= 1.5e8;
 }
 
-extern "C" dwfmm_status dwfmm_fmm_create(dwfmm_tree tree, dwfmm_kernel kernel, double q, const dwfmm_opts *opts,
-                                         void *stream, dwfmm_op *out)
+// dwfmm_fmm_create; solves: the operator may run cg_run1 (the server's do not).
+static dwfmm_status create_op(dwfmm_tree tree, dwfmm_kernel kernel, double q, const dwfmm_opts *opts, void *stream,
+                              bool solves, dwfmm_op *out)
 {
     if (!out) return fail(DWFMM_E_INVALID, "out is NULL");
     *out = nullptr;
@@ -767,10 +785,13 @@ extern "C" dwfmm_status dwfmm_fmm_create(dwfmm_tree tree, dwfmm_kernel kernel, d
     op->b_Vinv = dVinv;
     op->b_nnz = nnz_max;
     op->b_nleg = (int)leg_axis.size();
-    op->lookahead = cg_lookahead(tree, nx, o.check_every);
+    op->lookahead = solves && cg_lookahead(tree, nx, o.check_every) && g_pinned.prepare();
     if ((e = hipStreamCreateWithFlags(&op->fork.side, hipStreamNonBlocking)) != hipSuccess ||
         (e = hipEventCreateWithFlags(&op->fork.forked, hipEventDisableTiming)) != hipSuccess ||
-        (e = hipEventCreateWithFlags(&op->fork.joined, hipEventDisableTiming)) != hipSuccess) {
+        (e = hipEventCreateWithFlags(&op->fork.joined, hipEventDisableTiming)) != hipSuccess ||
+        (op->lookahead &&
+         ((e = hipEventCreateWithFlags(&op->state_read[0], hipEventDisableTiming)) != hipSuccess ||
+          (e = hipEventCreateWithFlags(&op->state_read[1], hipEventDisableTiming)) != hipSuccess))) {
         op->arena.release();
         delete op;
         return fail(DWFMM_E_HIP, std::string("operator streams: ") + hipGetErrorString(e));
@@ -779,6 +800,12 @@ extern "C" dwfmm_status dwfmm_fmm_create(dwfmm_tree tree, dwfmm_kernel kernel, d
     tree->refs++;
     *out = op;
     return DWFMM_OK;
+}
+
+extern "C" dwfmm_status dwfmm_fmm_create(dwfmm_tree tree, dwfmm_kernel kernel, double q, const dwfmm_opts *opts,
+                                         void *stream, dwfmm_op *out)
+{
+    return create_op(tree, kernel, q, opts, stream, true, out);
 }
 
 // Device bytes dwfmm_fmm_create allocates for an operator with basis B and workspace for R
@@ -1099,18 +1126,13 @@ hipError_t cg_run1(dwfmm_op op, double lambda, const double *b, double *x, doubl
     // Small problems look at a check's state one iteration late, while that iteration runs: the copy, the
     // wake-up and the next launches take about 20 us, which a short matvec does not cover, for one matvec
     // too many at the end (the vector steps of a stopped problem do nothing, so the results are the same).
-    if (op->lookahead && !op->progress && !op->h_state) {
-        for (hipEvent_t &ev : op->state_read)
-            if (!ev && (e = hipEventCreateWithFlags(&ev, hipEventDisableTiming)) != hipSuccess) return e;
-        op->h_state = g_pinned.take();
-    }
-    const bool ahead = op->h_state && !op->progress;
+    const PinnedSlot state(op->lookahead && !op->progress, st);
     for (int k = 0; k < max_iter; ++k) {
-        if (ahead) {
+        if (state.p) {
             const int ce = op->check_every;
             if (k % ce == 0) {
                 const int i = (k / ce) & 1;
-                if ((e = hipMemcpyAsync(op->h_state + i, op->state, sizeof(int32_t), hipMemcpyDeviceToHost, st)) !=
+                if ((e = hipMemcpyAsync(state.p + i, op->state, sizeof(int32_t), hipMemcpyDeviceToHost, st)) !=
                         hipSuccess ||
                     (e = hipEventRecord(op->state_read[i], st)) != hipSuccess)
                     return e;
@@ -1118,7 +1140,7 @@ hipError_t cg_run1(dwfmm_op op, double lambda, const double *b, double *x, doubl
             if (k > 0 && (k - 1) % ce == 0) {
                 const int i = ((k - 1) / ce) & 1;
                 if ((e = hipEventSynchronize(op->state_read[i])) != hipSuccess) return e;
-                if (op->h_state[i] != 0) break;
+                if (state.p[i] != 0) break;
             }
         } else if (k % op->check_every == 0) {
             if ((e = hipMemcpyAsync(hstate.data(), op->state, sizeof(int32_t), hipMemcpyDeviceToHost, st)) !=
@@ -2193,7 +2215,7 @@ dwfmm_status prepare_request(ServerRequest *r, hipStream_t ws)
     o.precision = r->precision;
     o.max_nrhs = 1;
     o.check_every = 1;
-    rc = dwfmm_fmm_create(r->tree, r->kernel, r->q, &o, ws, &r->op);
+    rc = create_op(r->tree, r->kernel, r->q, &o, ws, false, &r->op);
     if (rc != DWFMM_OK) return rc;
     const size_t nb = sizeof(double) * r->n;
     HIP_TRY(hipMalloc(&r->d_alpha, nb));
