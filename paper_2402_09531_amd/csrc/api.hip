@@ -1506,20 +1506,20 @@ static dwfmm_status batch_build(const dwfmm_op *ops, int32_t count, int32_t flag
     P.leaf_cnt = (int)work.size();
     // M2M and L2L: the k-th launch holds the k-th level group of every problem
     for (const bool up : {true, false}) {
-        std::vector<std::vector<XferGroup>> groups(b->items.size());
-        size_t most = 0;
+        std::vector<XferGroups> groups(b->items.size());
+        int most = 0;
         for (size_t it = 0; it < b->items.size(); ++it) {
             const BatchItem &I = b->items[it];
             if (!I.far) continue;
             groups[it] = up ? xfer_groups(true, I.O.nx, 1, I.T.min_far_level, I.T.J - 1)
                             : xfer_groups(false, I.O.nx, 1, I.T.min_far_level + 1, I.T.J);
-            most = std::max(most, groups[it].size());
+            most = std::max(most, groups[it].n);
         }
-        for (size_t k = 0; k < most; ++k) {
+        for (int k = 0; k < most; ++k) {
             const int off = (int)work.size();
             for (size_t it = 0; it < groups.size(); ++it) {
-                if (k >= groups[it].size()) continue;
-                const XferGroup g = groups[it][k];
+                if (k >= groups[it].n) continue;
+                const XferGroup g = groups[it].g[k];
                 for (int c = (1 << g.root) - 1; c < (1 << (g.root + 1)) - 1; ++c)
                     work.push_back(make_int2((int)it | g.depth << kXferDepthBit, c));
             }

@@ -142,29 +142,35 @@ struct BatchItem {
 struct XferGroup {
     int root, depth;
 };
+struct XferGroups {
+    int n = 0;
+    XferGroup g[32];  // a tree has at most 32 levels
+    const XferGroup *begin() const { return g; }
+    const XferGroup *end() const { return g + n; }
+};
 // The launches of M2M over levels hi, ..., lo (up) or L2L over levels lo, ..., hi, in order.  A
 // launch costs about 5 us however little it does and a level inside one about 1 us, so levels are
 // joined while a workgroup's subtree stays within 4000 cycles of products (1.7 us), or where the
 // launch has 2048 workgroups (8 per CU) anyhow.  Cycles of one CU per cluster: one rhs about 24
 // terms a cycle over its threads; several rhs 64 per FP64 MFMA on four SIMDs.
-inline std::vector<XferGroup> xfer_groups(bool up, int nx, int nrhs, int lo, int hi)
+inline XferGroups xfer_groups(bool up, int nx, int nrhs, int lo, int hi)
 {
     const int64_t src = up ? 2 : 1, nxt = (nx + 15) / 16, rb = (nrhs + 15) / 16;
     const int64_t cyc = nrhs == 1 ? std::max<int64_t>(1, src * nx * nx / 24) : src * nxt * rb * ((nx + 3) / 4) * 16;
     auto join = [&](int root, int depth) { return cyc * (((int64_t)1 << depth) - 1) <= 4000 || root >= 11; };
-    std::vector<XferGroup> g;
+    XferGroups g;
     if (up) {
         for (int j = hi; j >= lo;) {
             int r = j;
             while (r > lo && join(r - 1, j - r + 2)) --r;
-            g.push_back({r, j - r + 1});
+            g.g[g.n++] = {r, j - r + 1};
             j = r - 1;
         }
     } else {
         for (int j = lo; j <= hi;) {
             int depth = 1;
             while (j + depth <= hi && join(j, depth + 1)) ++depth;
-            g.push_back({j, depth});
+            g.g[g.n++] = {j, depth};
             j += depth;
         }
     }
