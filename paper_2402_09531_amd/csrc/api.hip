@@ -1468,7 +1468,6 @@ static dwfmm_status batch_build(const dwfmm_op *ops, int32_t count, int32_t flag
     if (!out) return fail(DWFMM_E_INVALID, "out is NULL");
     *out = nullptr;
     if (!ops || count < 1) return fail(DWFMM_E_INVALID, "ops is NULL or count < 1");
-    if (count >= 1 << kXferDepthBit) return fail(DWFMM_E_INVALID, "too many operators");
     for (int i = 0; i < count; ++i)
         if (!ops[i]) return fail(DWFMM_E_INVALID, "ops contains NULL");
     const int forced = (flags >> 4) & 7;
@@ -1509,19 +1508,19 @@ static dwfmm_status batch_build(const dwfmm_op *ops, int32_t count, int32_t flag
         std::vector<XferGroups> groups(b->items.size());
         int most = 0;
         for (size_t it = 0; it < b->items.size(); ++it) {
-            const BatchItem &I = b->items[it];
+            BatchItem &I = b->items[it];
             if (!I.far) continue;
             groups[it] = up ? xfer_groups(true, I.O.nx, 1, I.T.min_far_level, I.T.J - 1)
                             : xfer_groups(false, I.O.nx, 1, I.T.min_far_level + 1, I.T.J);
+            for (const XferGroup &g : groups[it]) (up ? I.up_depth : I.down_depth)[g.root] = (uint8_t)g.depth;
             most = std::max(most, groups[it].n);
         }
         for (int k = 0; k < most; ++k) {
             const int off = (int)work.size();
             for (size_t it = 0; it < groups.size(); ++it) {
                 if (k >= groups[it].n) continue;
-                const XferGroup g = groups[it].g[k];
-                for (int c = (1 << g.root) - 1; c < (1 << (g.root + 1)) - 1; ++c)
-                    work.push_back(make_int2((int)it | g.depth << kXferDepthBit, c));
+                const int root = groups[it].g[k].root;
+                for (int c = (1 << root) - 1; c < (1 << (root + 1)) - 1; ++c) work.push_back(make_int2((int)it, c));
             }
             (up ? P.m2m : P.l2l).push_back({off, (int)work.size() - off});
         }

@@ -135,6 +135,8 @@ struct BatchItem {
     DevOp O;
     int far;        // the problem has a farfield
     int precision;  // 0 FP64, 1/2 FP32 nearfield and coupling
+    // levels of the M2M (up) and L2L groups by the level of their root, 0 where no group starts
+    uint8_t up_depth[32], down_depth[32];
 };
 
 // M2M (up) and L2L passes: consecutive tree levels run by one launch, one workgroup per cluster of
@@ -176,7 +178,6 @@ inline XferGroups xfer_groups(bool up, int nx, int nrhs, int lo, int hi)
     }
     return g;
 }
-constexpr int kXferDepthBit = 24;
 
 // One launch of a templated kernel over a slice of the work list.  wpc (M2L only): waves per
 // target cluster, 4, 2 or 1; every choice gives bitwise the same locals.
@@ -195,7 +196,7 @@ struct BatchPlan {
     double *const *ys = nullptr;
     const int2 *work = nullptr;
     int leaf_off = 0, leaf_cnt = 0;
-    // (offset, count) per launch: entries (item | depth << kXferDepthBit, root cluster)
+    // (offset, count) per launch: entries (item, root cluster)
     std::vector<std::pair<int, int>> m2m, l2l;
     std::vector<BatchLaunch> m2l, p2p;
 };

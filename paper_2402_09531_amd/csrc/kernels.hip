@@ -3136,19 +3136,21 @@ __global__ __launch_bounds__(256) void p2m_batch_kernel(const BatchItem *items, 
     p2m_body(B.T, B.O, wk.y, xs[wk.x], 1, B.far, xl);
 }
 
-// (a work entry is a subtree root, its depth in the item's bits from kXferDepthBit)
+// (a work entry is a subtree root; the item holds the depth by the root's level)
 __global__ __launch_bounds__(256) void m2m_batch_kernel(const BatchItem *items, const int2 *work)
 {
     const int2 wk = work[blockIdx.x];
     if (wk.x < 0) return;
-    xfer_body<0, true>(items[wk.x & ((1 << kXferDepthBit) - 1)].O, wk.y, wk.x >> kXferDepthBit, 1);
+    const BatchItem &B = items[wk.x];
+    xfer_body<0, true>(B.O, wk.y, B.up_depth[31 - __clz(wk.y + 1)], 1);
 }
 
 __global__ __launch_bounds__(256) void l2l_batch_kernel(const BatchItem *items, const int2 *work)
 {
     const int2 wk = work[blockIdx.x];
     if (wk.x < 0) return;
-    xfer_body<0, false>(items[wk.x & ((1 << kXferDepthBit) - 1)].O, wk.y, wk.x >> kXferDepthBit, 1);
+    const BatchItem &B = items[wk.x];
+    xfer_body<0, false>(B.O, wk.y, B.down_depth[31 - __clz(wk.y + 1)], 1);
 }
 
 // 4 / WPC clusters of the work list per workgroup and pass; slots past the end or on padding
