@@ -1279,7 +1279,8 @@ constexpr int kSX64 = kSymLeaf + 16;
 // kernel has without it, at most the four that its registers allow.  (The square operator's Matern
 // runs the clamped kernel here: see kExpInRange.)
 constexpr int mrhs_lds(int dk, int rb) { return 8 * (dk * (kSX64 + 1) + kSymLeaf * (rb == 0 ? 3 : 16 * rb + 2)) + 4 * (2 * kSymSeg + 2 * kSymLeaf + 8); }
-constexpr int mrhs_wgs(int lds) { return 163840 / lds < 4 ? 163840 / lds : 4; }
+constexpr int kLds = 163840;  // of a CU, and the most a workgroup may have
+constexpr int mrhs_wgs(int lds) { return kLds / lds < 4 ? kLds / lds : 4; }
 // The split Gaussian of the square operator keeps the polynomial, since its matvec closes the
 // refinement solves of the reduced precisions (a last bit there moved their alpha by 5e-9).
 template <int KIND, int DK, int RB, bool CROSS>
@@ -1461,6 +1462,7 @@ __device__ __forceinline__ void p2p_mrhs_body(const DevTree &T, const DevOp &O, 
     const int n = T.n, ns_all = CROSS ? Ts.n : n;
     const double inv_ell = 1.0 / O.ell;
     const int ntiles = (nt + 15) / 16;
+    static_assert(mrhs_lds(DK, RB) + (mrhs_tab<KIND, DK, RB, CROSS>() ? 8 * kExp2Size : 0) <= kLds);
     __shared__ uint2 tab[mrhs_tab<KIND, DK, RB, CROSS>() ? kExp2Size : 1];
     if constexpr (mrhs_tab<KIND, DK, RB, CROSS>()) load_exp2_table(tab);
     // the shift: the leaf's box midpoint, or (target trees of evaluation plans) the first target
@@ -3733,8 +3735,8 @@ hipError_t launch_matvec(const DevTree &T, const DevOp &O, const double *x, doub
     const int far = (parts & 2) && T.min_far_level <= T.J;
     // symmetric MFMA nearfield for one rhs, leaves <= 128 points, d <= 32, radial kernels
     const bool sym = nrhs == 1 && O.kind <= 2 && T.max_leaf <= kSymLeaf && T.d <= 32 && O.rowbuf && O.colbuf;
-    // MFMA nearfield for several rhs (LDS of the FP64 kernel: at most 66 KB, at d <= 28 with two
-    // 16-wide rhs tiles; gfx950 gives a workgroup up to 160 KB)
+    // MFMA nearfield for several rhs (LDS of the FP64 kernel: at most 77 KB, at d <= 28 with two 16-wide
+    // rhs tiles and the table, so two workgroups per CU)
     const int dk = (T.d + 3) / 4 * 4;
     // (leaves above kSymLeaf points: FP64 in every precision mode, one rhs too)
     const bool mrhs = (nrhs > 1 || T.max_leaf > kSymLeaf) && O.kind <= 2 && dk <= 32 && !(dk > 28 && nrhs > 16);
@@ -3986,7 +3988,7 @@ hipError_t launch_eval(const DevTree &Tt, const DevOp &Ot, const DevTree &Ts, co
         launch_xfer<false>(Ot, Tt.min_far_level + 1, Tt.J, nrhs, st);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    // MFMA nearfield (66 KB of LDS at most, as the several-rhs nearfield)
+    // MFMA nearfield (at most 77 KB of LDS, as the several-rhs nearfield)
     if (radial && !(Tt.dpad > 28 && nrhs > 16)) return launch_pieces(Tt, Ot, Ts, Os.xt, y, nrhs, 1, far, st);
     switch (Os.kind) {
     case 0: return launch_p2p_cross_k<0>(Tt, Ot, Ts, Os.xt, y, nrhs, far, st);
