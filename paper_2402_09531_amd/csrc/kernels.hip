@@ -904,10 +904,15 @@ constexpr int kGaussSplit = 4;
 // without the underflow clamp.
 constexpr int kMaternInRange = 5;
 // The same for the exponential kernel (exp_in_range): no clamp, coordinates scaled by log2(e) / ell and
-// 2^-s from the table in LDS.  It and the split Gaussian use the table; the clamped kernels keep the
-// polynomial (the table with a clamp and subnormal results was 2.5% slower at d = 7), and so does
-// Matern: CG amplifies the last bit of a matvec (1e-15) to 1e-8 in a solution that stopped at 1e-8,
-// and the solves of that kernel were to keep their results.
+// 2^-s from the table in LDS.  Where the table serves: the split Gaussian and the exponential in range of
+// the symmetric nearfield (one rhs, batches: also inside CG and as the FP64 residual of refinements), the
+// exponential in range with several rhs, and all three kernels in range of the nearfield of pieces
+// (evaluation and leaves above 128 points).  The polynomial serves the clamped kernels (the table with a
+// clamp and subnormal results was 2.5% slower at d = 7) and, on trees with leaves of at most 128 points, Matern
+// and the several-rhs split Gaussian.  These two are not a matter of accuracy: the table is no further off
+// and took 6 to 7% off a batch of Matern problems and the server.  Their matvecs close solves that stop at
+// 1e-8, whose solutions moved within that tolerance (by 9e-8 of Matern solutions, 5e-9 of refined Gaussian ones), and
+// were to stay as they are.
 constexpr int kExpInRange = 6;
 template <int KIND>
 constexpr bool uses_tab() { return KIND == kGaussSplit || KIND == kExpInRange; }
@@ -1120,12 +1125,14 @@ __device__ __forceinline__ void p2p_sym_body(const DevTree &T, const DevOp &O, i
             // 2.34 ms), nothing at the other d; |x|^2 added to the tile instead cost 3 to 5 % at d <= 12.
             double t = s;
             if constexpr (KIND == 2 || KIND == kExpInRange) {
+                if (!nk) {
 #pragma unroll
-                for (int k = 0; k < DK; ++k) {
-                    const double v = sX[k * kSymLeaf + j];
-                    t = fma(-2.0 * v, v, t);
+                    for (int k = 0; k < DK; ++k) {
+                        const double v = sX[k * kSymLeaf + j];
+                        t = fma(-2.0 * v, v, t);
+                    }
+                    t = -t;
                 }
-                t = -t;
             }
             sN[nb + j] = t;
             sQ[j] = ok ? q : 0.0;
@@ -1276,13 +1283,12 @@ __device__ __forceinline__ int q_col(int j, int r) { return RB == 2 ? r ^ ((j & 
 constexpr int kSX64 = kSymLeaf + 16;
 // LDS of the kernel below without the exp2 table, and whether the table (8 KB) is used: by the
 // kernels in range and the split Gaussian where it leaves as many workgroups per CU (160 KB) as the
-// kernel has without it, at most the four that its registers allow.  (The square operator's Matern
-// runs the clamped kernel here: see kExpInRange.)
+// kernel has without it, at most the four that its registers allow.  (Matern with leaves of at most 128
+// points runs the clamped kernel here: see kExpInRange.)
 constexpr int mrhs_lds(int dk, int rb) { return 8 * (dk * (kSX64 + 1) + kSymLeaf * (rb == 0 ? 3 : 16 * rb + 2)) + 4 * (2 * kSymSeg + 2 * kSymLeaf + 8); }
 constexpr int kLds = 163840;  // of a CU, and the most a workgroup may have
 constexpr int mrhs_wgs(int lds) { return kLds / lds < 4 ? kLds / lds : 4; }
-// The split Gaussian of the square operator keeps the polynomial, since its matvec closes the
-// refinement solves of the reduced precisions (a last bit there moved their alpha by 5e-9).
+// The split Gaussian with leaves of at most 128 points keeps the polynomial (see kExpInRange).
 template <int KIND, int DK, int RB, bool CROSS>
 constexpr bool mrhs_tab()
 {
@@ -2889,7 +2895,7 @@ void launch_m2l_mrhs_cross_k(const DevTree &T, const DevOp &Ot, const DevOp &Os,
 // apply MFMA; RB = 0 (one rhs) sums on the vector ALU.  Bound by the FP64 pipe (four waves per SIMD up
 // to d = 20, by the attribute: the target frame's registers would leave three, 2 % slower); against the general
 // kernel (one thread per coupling entry, S through LDS) at N = 1e5, d = 20, n_x = 97, 25 rhs:
-// 35.8 -> 4.6 ms.
+// 35.8 -> 4.25 ms.
 template <int KIND, int DK, int RB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DK <= 20 ? 4 : 1, 8)))
 void m2l_wide_kernel(DevTree T, DevOp O, DevOp Os, int first, int nrhs)
