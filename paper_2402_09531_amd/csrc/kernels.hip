@@ -129,7 +129,7 @@ __device__ __forceinline__ double exp2_tab_split(double m, double f, const uint2
 // and three integer operations and one LDS read per value against exp2_bounded's fourteen, and no
 // further off (half an ulp each from the table and the last operation, 9.4e-17 from the cubic).  The
 // FP64 pipe bounds these kernels, so the slots are time: N = 1e6, d = 20 split Gaussian one rhs
-// 11.9 -> 10.95 ms per matvec; N = 3e5, d = 20 exponential 2.64 -> 2.31 ms (with the scaled
+// 11.9 -> 10.95 ms per matvec; N = 3e5, d = 20 exponential 2.64 -> 2.34 ms (with the scaled
 // coordinates below); 2e5 targets and sources, d = 20 Gaussian evaluation 2.25 -> 1.97 ms.
 __device__ __forceinline__ double exp2_tab(double t, const uint2 *tab)
 {
