@@ -1301,7 +1301,9 @@ constexpr bool mrhs_tab()
 // rho = sqrt(N) / ell: eps rho for the exponential's square root of a tiny r^2 and 1.5 eps rho^2 for Matern,
 // eps rho^2 for the Gaussian (direct or split).  So
 //   - r^2 < kNear N: the differences of the coordinates instead, for the exponential (no cost: d = 6,
-//     1e5 sources, 5e4 targets 1.25 ms with 1e-4 and 1e-2 alike) and the clamped kernels.  What is left is
+//     1e5 sources, 5e4 targets 1.25 ms with 1e-4 and 1e-2 alike) and the clamped kernels.  One branch for the
+//     four entries of a lane: with one each, a few targets per leaf (4e4 sources, 3001 targets) took 5 to
+//     12 % more (d = 4: 318 us, 357; d = 20: 244, 263).  What is left is
 //     eps rho exp(-sqrt(kNear) rho) / (2 sqrt(kNear)), 0.8 eps / kNear for Matern, 0.4 eps / kNear for
 //     the Gaussian: 1e-14 and less at any rho;
 //   - Matern in range and the split Gaussian have no such branch (it cost Matern 5 to 9 %) and are taken only
@@ -1382,40 +1384,48 @@ __device__ __forceinline__ void mrhs_block(const double (&Bt)[2][DK / 4], const 
 #pragma unroll
                 for (int kc = 0; kc < NKC; ++kc) G = __builtin_amdgcn_mfma_f64_16x16x4f64(Af[kc], Bt[u][kc], G, 0, 0, 0);
             }
-            double Kv[4];
+            double Kv[4], r2[4];
+            if constexpr (KIND != kGaussSplit) {
+                // (the kernels in range: the coordinates carry their scale, so r2 is s^2)
+                bool close = false;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                if constexpr (KIND == kGaussSplit) {
-                    Kv[v] = kTab ? exp2_tab(G[v], tab) : exp2_bounded(G[v]);
-                } else {
-                    // (the kernels in range: the coordinates carry their scale, so r2 is s^2)
-                    double r2;
+                for (int v = 0; v < 4; ++v) {
                     if constexpr (kDiff) {
-                        r2 = 0.0;
+                        r2[v] = 0.0;
 #pragma unroll
                         for (int k = 0; k < 4; ++k) {
                             const double t = tx[u][k] - sx[k][v];
-                            r2 = fma(t, t, r2);
+                            r2[v] = fma(t, t, r2[v]);
                         }
                     } else {
-                        r2 = fma(-2.0, G[v], tn[u] + snv[v]);
-                        if constexpr (KIND != kExpInRange && KIND != kMaternInRange) r2 = fmax(r2, 0.0);
+                        r2[v] = fma(-2.0, G[v], tn[u] + snv[v]);
+                        if constexpr (KIND != kExpInRange && KIND != kMaternInRange) r2[v] = fmax(r2[v], 0.0);
                     }
                     if constexpr (DIAG) {
-                        if (16 * rt[u] + li == 16 * ct + 4 * v + lg) r2 = 0.0;
+                        if (16 * rt[u] + li == 16 * ct + 4 * v + lg) r2[v] = 0.0;
                     }
-                    if constexpr (kNear > 0.0) {
-                        // (never a padding column: it sits on the shift, r2 is tn)
-                        if (r2 < kNear * (tn[u] + snv[v]))
-                            r2 = csc * csc * r2_direct<DK>(T, Ts, near_i[u], sP[16 * ct + 4 * v + lg]);
-                    }
-                    if constexpr (KIND == kExpInRange)
-                        Kv[v] = exponential_s2<kTab>(fmax(r2, 1e-300), tab);
-                    else if constexpr (KIND == kMaternInRange)
-                        Kv[v] = kTab ? matern_s2_tab(r2, tab) : matern_s2<false>(r2);
-                    else
-                        Kv[v] = kernel_fast<KIND>(r2, inv_ell);
+                    // (never a padding column: it sits on the shift, r2 is tn)
+                    if constexpr (kNear > 0.0) close |= r2[v] < kNear * (tn[u] + snv[v]);
                 }
+                if constexpr (kNear > 0.0) {
+                    if (close) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            if (r2[v] < kNear * (tn[u] + snv[v]))
+                                r2[v] = csc * csc * r2_direct<DK>(T, Ts, near_i[u], sP[16 * ct + 4 * v + lg]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                if constexpr (KIND == kGaussSplit)
+                    Kv[v] = kTab ? exp2_tab(G[v], tab) : exp2_bounded(G[v]);
+                else if constexpr (KIND == kExpInRange)
+                    Kv[v] = exponential_s2<kTab>(fmax(r2[v], 1e-300), tab);
+                else if constexpr (KIND == kMaternInRange)
+                    Kv[v] = kTab ? matern_s2_tab(r2[v], tab) : matern_s2<false>(r2[v]);
+                else
+                    Kv[v] = kernel_fast<KIND>(r2[v], inv_ell);
             }
             if constexpr (RB == 0) {
 #pragma unroll
