@@ -208,13 +208,13 @@ __device__ __forceinline__ double matern_s2_tab(double s2, const uint2 *tab)
     return fma(s, e, e);
 }
 
-// e^(-r / ell) from s^2 = (r log2(e) / ell)^2 >= 1e-300, for callers whose coordinates are already scaled
-// by log2(e) / ell and that guarantee s <= 1000 and clamp s^2 (its rounding may be below zero): 2^-s (from
-// the table if TAB).
+// e^(-r / ell) from s^2 = (r log2(e) / ell)^2, for callers whose coordinates are already scaled by
+// log2(e) / ell and that guarantee s <= 1000: the guard of matern_s2 (a maximum instead is 1 % slower), then
+// 2^-s (from the table if TAB).
 template <bool TAB>
 __device__ __forceinline__ double exponential_s2(double s2, const uint2 *tab)
 {
-    const double t = -sqrt_pos(s2);
+    const double t = -sqrt_pos(fabs(s2) + 1e-300);
     return TAB ? exp2_tab(t, tab) : exp2_bounded(t);
 }
 
@@ -973,8 +973,7 @@ __device__ __forceinline__ void sym_block(const double (&A)[2][NKC], const doubl
                     if constexpr (is_matern<KIND>())
                         kv = matern_s2<KIND == 0>(r2);
                     else if constexpr (KIND == kExpInRange)
-                        // (an MFMA result: the absolute value is free, fmax would canonicalise it first)
-                        kv = exponential_s2<true>(NK ? fabs(r2) + 1e-300 : fmax(r2, 1e-300), tab);
+                        kv = exponential_s2<true>(r2, tab);
                     else
                         kv = kernel_fast<KIND>(r2, inv_ell);
                 }
@@ -1384,48 +1383,53 @@ __device__ __forceinline__ void mrhs_block(const double (&Bt)[2][DK / 4], const 
 #pragma unroll
                 for (int kc = 0; kc < NKC; ++kc) G = __builtin_amdgcn_mfma_f64_16x16x4f64(Af[kc], Bt[u][kc], G, 0, 0, 0);
             }
-            double Kv[4], r2[4];
-            if constexpr (KIND != kGaussSplit) {
-                // (the kernels in range: the coordinates carry their scale, so r2 is s^2)
+            double Kv[4];
+            // (the kernels in range: the coordinates carry their scale, so r2 is s^2)
+            auto dist2 = [&](int v) {
+                double r2;
+                if constexpr (kDiff) {
+                    r2 = 0.0;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const double t = tx[u][k] - sx[k][v];
+                        r2 = fma(t, t, r2);
+                    }
+                } else {
+                    r2 = fma(-2.0, G[v], tn[u] + snv[v]);
+                    if constexpr (KIND != kExpInRange && KIND != kMaternInRange) r2 = fmax(r2, 0.0);
+                }
+                if constexpr (DIAG) {
+                    if (16 * rt[u] + li == 16 * ct + 4 * v + lg) r2 = 0.0;
+                }
+                return r2;
+            };
+            auto value = [&](double r2) {
+                if constexpr (KIND == kExpInRange) return exponential_s2<kTab>(r2, tab);
+                else if constexpr (KIND == kMaternInRange) return kTab ? matern_s2_tab(r2, tab) : matern_s2<false>(r2);
+                else return kernel_fast<KIND>(r2, inv_ell);
+            };
+            if constexpr (KIND == kGaussSplit) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) Kv[v] = kTab ? exp2_tab(G[v], tab) : exp2_bounded(G[v]);
+            } else if constexpr (kNear > 0.0) {
+                // (never a padding column: it sits on the shift, r2 is tn)
                 bool close = false;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    if constexpr (kDiff) {
-                        r2[v] = 0.0;
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            const double t = tx[u][k] - sx[k][v];
-                            r2[v] = fma(t, t, r2[v]);
-                        }
-                    } else {
-                        r2[v] = fma(-2.0, G[v], tn[u] + snv[v]);
-                        if constexpr (KIND != kExpInRange && KIND != kMaternInRange) r2[v] = fmax(r2[v], 0.0);
-                    }
-                    if constexpr (DIAG) {
-                        if (16 * rt[u] + li == 16 * ct + 4 * v + lg) r2[v] = 0.0;
-                    }
-                    // (never a padding column: it sits on the shift, r2 is tn)
-                    if constexpr (kNear > 0.0) close |= r2[v] < kNear * (tn[u] + snv[v]);
+                    Kv[v] = dist2(v);
+                    close |= Kv[v] < kNear * (tn[u] + snv[v]);
                 }
-                if constexpr (kNear > 0.0) {
-                    if (close) {
+                if (close) {
 #pragma unroll
-                        for (int v = 0; v < 4; ++v)
-                            if (r2[v] < kNear * (tn[u] + snv[v]))
-                                r2[v] = csc * csc * r2_direct<DK>(T, Ts, near_i[u], sP[16 * ct + 4 * v + lg]);
-                    }
+                    for (int v = 0; v < 4; ++v)
+                        if (Kv[v] < kNear * (tn[u] + snv[v]))
+                            Kv[v] = csc * csc * r2_direct<DK>(T, Ts, near_i[u], sP[16 * ct + 4 * v + lg]);
                 }
-            }
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                if constexpr (KIND == kGaussSplit)
-                    Kv[v] = kTab ? exp2_tab(G[v], tab) : exp2_bounded(G[v]);
-                else if constexpr (KIND == kExpInRange)
-                    Kv[v] = exponential_s2<kTab>(fmax(r2[v], 1e-300), tab);
-                else if constexpr (KIND == kMaternInRange)
-                    Kv[v] = kTab ? matern_s2_tab(r2[v], tab) : matern_s2<false>(r2[v]);
-                else
-                    Kv[v] = kernel_fast<KIND>(r2[v], inv_ell);
+                for (int v = 0; v < 4; ++v) Kv[v] = value(Kv[v]);
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) Kv[v] = value(dist2(v));
             }
             if constexpr (RB == 0) {
 #pragma unroll
@@ -1697,8 +1701,8 @@ __device__ __forceinline__ void p2p_mrhs_body(const DevTree &T, const DevOp &O, 
 }
 
 template <int KIND, int DK, int RB>
-__global__ __launch_bounds__(256) void p2p_mrhs_kernel(DevTree T, DevOp O, double *__restrict__ y, int nrhs,
-                                                       int do_near, int do_far)
+__global__ __launch_bounds__(256) void p2p_mrhs_kernel(
+    DevTree T, DevOp O, double *__restrict__ y, int nrhs, int do_near, int do_far)
 {
     p2p_mrhs_body<KIND, DK, RB, false>(T, O, T, O.xt, y, nrhs, do_near, do_far);
 }
@@ -1709,8 +1713,9 @@ __global__ __launch_bounds__(256) void p2p_mrhs_kernel(DevTree T, DevOp O, doubl
 // exponential, leaf 256, 25 rhs 223.6 -> 4.6 ms; 1e5 sources, 5e4 targets, d = 10 Matern, 8 rhs
 // 69.6 -> 2.0 ms.
 template <int KIND, int DK, int RB>
-__global__ __launch_bounds__(256) void p2p_pieces_kernel(DevTree T, DevOp O, DevTree Ts, const double *__restrict__ xs,
-                                                         double *__restrict__ y, int nrhs, int do_near, int do_far)
+__global__ __launch_bounds__(256) void p2p_pieces_kernel(
+    DevTree T, DevOp O, DevTree Ts, const double *__restrict__ xs, double *__restrict__ y, int nrhs, int do_near,
+    int do_far)
 {
     p2p_mrhs_body<KIND, DK, RB, true>(T, O, Ts, xs, y, nrhs, do_near, do_far);
 }
