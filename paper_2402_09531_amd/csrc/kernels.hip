@@ -1700,8 +1700,10 @@ __device__ __forceinline__ void p2p_mrhs_body(const DevTree &T, const DevOp &O, 
     }
 }
 
+// (Two waves per SIMD by the attribute: at d = 32 the kernels other than the split Gaussian otherwise take
+// a few registers more than allow it, and N = 4e4, d = 31, 9 rhs, Matern takes 614 us instead of 812.)
 template <int KIND, int DK, int RB>
-__global__ __launch_bounds__(256) void p2p_mrhs_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DK > 28 ? 2 : 1, 8))) void p2p_mrhs_kernel(
     DevTree T, DevOp O, double *__restrict__ y, int nrhs, int do_near, int do_far)
 {
     p2p_mrhs_body<KIND, DK, RB, false>(T, O, T, O.xt, y, nrhs, do_near, do_far);
@@ -1713,7 +1715,7 @@ __global__ __launch_bounds__(256) void p2p_mrhs_kernel(
 // exponential, leaf 256, 25 rhs 223.6 -> 4.6 ms; 1e5 sources, 5e4 targets, d = 10 Matern, 8 rhs
 // 69.6 -> 2.0 ms.
 template <int KIND, int DK, int RB>
-__global__ __launch_bounds__(256) void p2p_pieces_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DK > 28 ? 2 : 1, 8))) void p2p_pieces_kernel(
     DevTree T, DevOp O, DevTree Ts, const double *__restrict__ xs, double *__restrict__ y, int nrhs, int do_near,
     int do_far)
 {
