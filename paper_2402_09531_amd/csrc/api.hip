@@ -1126,6 +1126,7 @@ hipError_t cg_run1(dwfmm_op op, double lambda, const double *b, double *x, doubl
     // Small problems look at a check's state one iteration late, while that iteration runs: the copy, the
     // wake-up and the next launches take about 20 us, which a short matvec does not cover, for one matvec
     // too many at the end (the vector steps of a stopped problem do nothing, so the results are the same).
+    // The first state is waited for: a solve that is converged as it starts runs no iteration.
     const PinnedSlot state(op->lookahead && !op->progress, st);
     for (int k = 0; k < max_iter; ++k) {
         if (state.p) {
@@ -1137,8 +1138,9 @@ hipError_t cg_run1(dwfmm_op op, double lambda, const double *b, double *x, doubl
                     (e = hipEventRecord(op->state_read[i], st)) != hipSuccess)
                     return e;
             }
-            if (k > 0 && (k - 1) % ce == 0) {
-                const int i = ((k - 1) / ce) & 1;
+            const int look = k == 0 ? 0 : k - 1;
+            if (look % ce == 0 && k != 1) {
+                const int i = (look / ce) & 1;
                 if ((e = hipEventSynchronize(op->state_read[i])) != hipSuccess) return e;
                 if (state.p[i] != 0) break;
             }
